@@ -400,6 +400,24 @@ typedef struct {
 int shape_frame_detect(const shape_frames* frames, int32_t max_side, float* info, int32_t* peak,
                        int32_t* box, uint32_t* status, void* stream);
 
+/*
+ * The same with scratch memory of the caller's: the frames are read by as many
+ * workgroups as the card takes, not by one each, so a few large frames take
+ * microseconds where shape_frame_detect takes most of a millisecond.  The
+ * same outputs (sky and F are the same FP64 sums in another order, so their
+ * FP32 values may differ in the last bit).  ws (device, 16-byte aligned) is
+ * free again once the stream has passed the call; its contents are not used
+ * between calls.
+ *   shape_frame_workspace_bytes: the bytes ws needs for these frames (a
+ *   function of n, height, width and dtype).
+ * Errors: as shape_frame_detect; SHAPE_EINVAL for a NULL or misaligned ws,
+ * SHAPE_ENOMEM for too few bytes.
+ */
+int shape_frame_workspace_bytes(const shape_frames* frames, size_t* bytes);
+int shape_frame_detect_ws(const shape_frames* frames, int32_t max_side, float* info,
+                          int32_t* peak, int32_t* box, uint32_t* status, void* ws,
+                          size_t ws_bytes, void* stream);
+
 /* Exclusive prefix sums of side^2 over box [n][3] (device): offset [n] of each
  * cut-out in the packed stamps, and total [1] = their sum (pixels to
  * allocate).  n = 0 writes total = 0. */

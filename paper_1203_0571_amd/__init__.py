@@ -135,7 +135,10 @@ def _load():
     lib.shape_frame_detect.argtypes = [fp, C.c_int32, vp, vp, vp, vp, vp]
     lib.shape_frame_offsets.argtypes = [vp, C.c_int64, vp, vp, vp]
     lib.shape_frame_cut.argtypes = [fp, vp, vp, vp, C.c_int64, vp, vp]
-    for f in ("shape_frame_detect", "shape_frame_offsets", "shape_frame_cut"):
+    lib.shape_frame_workspace_bytes.argtypes = [fp, C.POINTER(C.c_size_t)]
+    lib.shape_frame_detect_ws.argtypes = [fp, C.c_int32, vp, vp, vp, vp, vp, C.c_size_t, vp]
+    for f in ("shape_frame_detect", "shape_frame_offsets", "shape_frame_cut",
+              "shape_frame_workspace_bytes", "shape_frame_detect_ws"):
         getattr(lib, f).restype = C.c_int
     qp = C.POINTER(QueueCfg)
     lib.shape_queue_default_cfg.argtypes = [qp]
@@ -446,13 +449,17 @@ def sersic_chi2(params: torch.Tensor, batch: DeviceBatch) -> torch.Tensor:
 
 
 def frame_detect(frames: DeviceFrames, max_side: int = 128):
-    """shape_frame_detect: dict(info [n,3] = sky, r50, F; peak [n,2]; box [n,3]; status)."""
+    """shape_frame_detect_ws: dict(info [n,3] = sky, r50, F; peak [n,2]; box [n,3]; status)."""
     n, dev = frames.n, frames.device
     info, peak, box, st = _outs(n, dev, ((n, 3), torch.float32), ((n, 2), torch.int32),
                                 ((n, 3), torch.int32), ((n,), torch.int32))
     f = frames.c_struct()
-    _check(lib.shape_frame_detect(C.byref(f), int(max_side), _ptr(info), _ptr(peak), _ptr(box),
-                                  _ptr(st), _stream(dev)), "shape_frame_detect")
+    nb = C.c_size_t()
+    _check(lib.shape_frame_workspace_bytes(C.byref(f), C.byref(nb)), "shape_frame_workspace_bytes")
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=dev)
+    _check(lib.shape_frame_detect_ws(C.byref(f), int(max_side), _ptr(info), _ptr(peak), _ptr(box),
+                                     _ptr(st), _ptr(ws), nb.value, _stream(dev)),
+           "shape_frame_detect_ws")
     return dict(info=info, peak=peak, box=box, status=st)
 
 

@@ -225,6 +225,28 @@ int shape_frame_detect(const shape_frames* f, int32_t max_side, float* info, int
   return from_hip(launch_frame_detect(*f, max_side, info, peak, box, status, (hipStream_t)stream));
 }
 
+int shape_frame_workspace_bytes(const shape_frames* f, size_t* bytes) {
+  int rc = check_frames(f);
+  if (rc != SHAPE_OK) return rc;
+  if (!bytes) return SHAPE_EINVAL;
+  *bytes = f->n ? frame_workspace_bytes(*f) : 0;
+  return SHAPE_OK;
+}
+
+int shape_frame_detect_ws(const shape_frames* f, int32_t max_side, float* info, int32_t* peak,
+                          int32_t* box, uint32_t* status, void* ws, size_t ws_bytes,
+                          void* stream) {
+  int rc = check_frames(f);
+  if (rc != SHAPE_OK) return rc;
+  if (max_side < 4 || max_side > 128) return SHAPE_EINVAL;
+  if (f->n == 0) return SHAPE_OK;
+  if (!info || !peak || !box || !status || !ws) return SHAPE_EINVAL;
+  if (reinterpret_cast<uintptr_t>(ws) % 16 != 0) return SHAPE_EINVAL;
+  if (ws_bytes < frame_workspace_bytes(*f)) return SHAPE_ENOMEM;
+  return from_hip(launch_frame_detect_ws(*f, max_side, info, peak, box, status, ws,
+                                         (hipStream_t)stream));
+}
+
 int shape_frame_offsets(const int32_t* box, int64_t n, int64_t* offset, int64_t* total,
                         void* stream) {
   if (n < 0 || !total || (n > 0 && (!box || !offset))) return SHAPE_EINVAL;

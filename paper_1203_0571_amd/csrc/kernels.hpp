@@ -67,6 +67,10 @@ hipError_t launch_stars(const shape_batch& b, int profile, const float* rec, dou
 int frame_bins(int height, int width);
 hipError_t launch_frame_detect(const shape_frames& f, int max_side, float* info, int32_t* peak,
                                int32_t* box, uint32_t* status, hipStream_t stream);
+// The same with scratch memory (frame_workspace_bytes, 16-byte aligned).
+size_t frame_workspace_bytes(const shape_frames& f);
+hipError_t launch_frame_detect_ws(const shape_frames& f, int max_side, float* info, int32_t* peak,
+                                  int32_t* box, uint32_t* status, void* ws, hipStream_t stream);
 hipError_t launch_frame_offsets(const int32_t* box, int64_t n, int64_t* offset, int64_t* total,
                                 hipStream_t stream);
 hipError_t launch_frame_cut(const shape_frames& f, const int32_t* box, const int64_t* offset,

@@ -261,6 +261,30 @@ def test_frame_argument_errors(shape):
     assert L.shape_frame_cut(C.byref(e), None, None, None, 0, None, None) == shape.OK
 
 
+def test_frame_workspace_errors(shape):
+    L = shape.lib
+    out, nb = C.c_void_p(0x3000), C.c_size_t()
+    f = _frames(shape)
+    assert L.shape_frame_workspace_bytes(C.byref(f), None) == shape.EINVAL
+    assert L.shape_frame_workspace_bytes(C.byref(_frames(shape, height=3)), C.byref(nb)) == shape.EINVAL
+    assert L.shape_frame_workspace_bytes(C.byref(f), C.byref(nb)) == shape.OK and nb.value > 0
+
+    def call(fr, ws=out, ws_bytes=nb.value, max_side=128, info=out):
+        return L.shape_frame_detect_ws(C.byref(fr), max_side, info, out, out, out, ws, ws_bytes, None)
+
+    assert call(f, ws=None) == shape.EINVAL
+    assert call(f, ws=C.c_void_p(0x3008)) == shape.EINVAL          # misaligned
+    assert call(f, ws_bytes=nb.value - 1) == shape.ENOMEM
+    assert call(f, info=None) == shape.EINVAL
+    for ms in (3, 129):
+        assert call(f, max_side=ms) == shape.EINVAL
+    for bad in [dict(n=-1), dict(width=4097), dict(dtype=7), dict(pixels=None)]:
+        assert call(_frames(shape, **bad)) == shape.EINVAL
+    e = _frames(shape, n=0, pixels=None)
+    assert L.shape_frame_workspace_bytes(C.byref(e), C.byref(nb)) == shape.OK and nb.value == 0
+    assert call(e, ws=None, ws_bytes=0) == shape.OK
+
+
 def test_unprofiled_form_is_limited_to_the_4_parameter_sersic_fit(shape):
     L = shape.lib
     out = C.c_void_p(0x3000)

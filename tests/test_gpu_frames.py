@@ -146,3 +146,61 @@ def test_frames_to_fitted_objects(shape):
     r = {"fit_" + k: v for k, v in st.items()}
     r.update(n=st["n"], fit_failures=failures)
     check_fit(r, 0.8)
+
+
+def _one_group_per_frame(shape, fr, max_side=128):
+    """shape_frame_detect (no scratch memory)."""
+    import ctypes as C
+
+    import torch
+    n, dev = fr.n, fr.device
+    out = dict(info=torch.empty(n, 3, device=dev),
+               peak=torch.empty(n, 2, dtype=torch.int32, device=dev),
+               box=torch.empty(n, 3, dtype=torch.int32, device=dev),
+               status=torch.empty(n, dtype=torch.int32, device=dev))
+    f = fr.c_struct()
+    rc = shape.lib.shape_frame_detect(C.byref(f), max_side, *(t.data_ptr() for t in out.values()),
+                                      None)
+    assert rc == shape.OK
+    torch.cuda.synchronize()
+    return {k: v.cpu().numpy() for k, v in out.items()}
+
+
+# Frame sizes around the split of a frame over workgroups: one chunk (a frame
+# below one batch of vectors), a frame of exactly one batch, several chunks
+# with a ragged last one, frames whose starts are not 16-byte aligned (odd
+# pixel counts), rows longer and much shorter than a chunk.
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("H,W", [(4, 5), (64, 64), (64, 128), (91, 93), (517, 333), (4096, 9),
+                                 (7, 4095)])
+def test_split_frames_match_one_workgroup_per_frame(shape, H, W, f16):
+    import torch
+    rng = np.random.default_rng(H * 5000 + W)
+    n = 6
+    pix = rng.normal(10.0, 1.0, (n, H, W)).astype(np.float32)
+    i, j = rng.integers(0, H, n), rng.integers(0, W, n)
+    pix[np.arange(n), i, j] += 100.0 + 20.0 * H * W ** 0.5
+    pix[1, -1, -1] = pix[1, 0, 0] = pix[1].max() + 64.0     # a tie, first and last pixel
+    pix[2, H - 1, W - 1] = np.nan
+    pix[3, 0, 0] = -np.inf
+    pix[4] = 0.25                                           # flat: F = 0
+    pix[5] -= pix[5].max()
+    pix[5, H // 2, 0] = 0.0                                 # peak on the border
+    scale = None
+    if f16:
+        scale = np.array([16.0, 16.0, 32.0, 16.0, 0.125, 16.0], np.float32)
+        pix = (pix / scale[:, None, None]).astype(np.float16)
+    fr, g = _gpu_detect(shape, pix, scale=scale)
+    ref = _one_group_per_frame(shape, fr)
+    torch.cuda.synchronize()
+    for k in ("peak", "box", "status"):
+        np.testing.assert_array_equal(g[k], ref[k], err_msg=k)
+    # the same FP64 sums in another order, stored in FP32: the last bit, and
+    # for F the rounding of sums of H W terms of size max |I|
+    np.testing.assert_allclose(g["info"][:, :2], ref["info"][:, :2], rtol=2.0 ** -22)
+    top = np.nan_to_num(np.abs(pix.astype(np.float64)).reshape(n, -1).max(1), posinf=0.0)
+    top *= scale if f16 else 1.0
+    ok = np.isfinite(ref["info"][:, 2])
+    assert (np.isfinite(g["info"][:, 2]) == ok).all()
+    tol = 2.0 ** -22 * np.abs(ref["info"][:, 2]) + 2.0 ** -50 * H * W * top
+    assert (np.abs(g["info"][:, 2] - ref["info"][:, 2])[ok] <= tol[ok]).all()
