@@ -347,16 +347,18 @@ int shape_queue_graph_destroy(shape_queue_graph* graph);
  * The work-queue fit in one call, with no allocation: for callers that cannot
  * allocate device memory (code under hipGraph/stream capture, tight serving
  * loops, harnesses that forbid hipMalloc).  Same inputs and outputs as
- * shape_fit_sersic plus the queue configuration; it runs shape_queue_start,
- * max_iter_lm steps (a step finds no work once every stamp is done) and
- * shape_queue_finish, with the workspace in a static device array of the
- * library (queue workspace of SHAPE_STATIC_MAX_STAMPS stamps, about 67 MB,
- * held on every device the library runs on until the process ends).  The
- * results equal those of the three calls with a caller's workspace.
+ * shape_fit_sersic plus the queue configuration, and the results of
+ * shape_queue_start, max_iter_lm steps and shape_queue_finish with a caller's
+ * workspace.  With cfg->team = 1 it runs the fused fit, whose results are the
+ * same and which needs no workspace; with teams it runs shape_queue_start,
+ * shape_queue_drain and shape_queue_finish with the workspace in a static
+ * device array of the library (queue workspace of SHAPE_STATIC_MAX_STAMPS
+ * stamps, about 67 MB, held on every device the library runs on until the
+ * process ends).
  *   n > SHAPE_STATIC_MAX_STAMPS returns SHAPE_ENOMEM before any work.
- * The array is shared by every call on a device: calls that overlap on one
- * device (several streams or host threads) race and must be serialised by
- * the caller.  Its device address is looked up on the first call on each
+ * The array is shared by every call with teams on a device: such calls that
+ * overlap on one device (several streams or host threads) race and must be
+ * serialised by the caller.  Its device address is looked up on the first call on each
  * device (hipGetSymbolAddress); make a first call outside stream capture.
  */
 #define SHAPE_STATIC_MAX_STAMPS 65536

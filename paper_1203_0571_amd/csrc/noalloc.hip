@@ -2,7 +2,8 @@
 // that cannot allocate device memory (code under stream capture, serving
 // loops, harnesses that forbid allocation): shape_fit_queue_static.
 //
-// The workspace is one file-scope device array.  In host code its name is a
+// At one wave per stamp the fit needs no workspace; teams of waves take the
+// queue's.  The workspace is one file-scope device array.  In host code its name is a
 // host-side stand-in, not a device address, so the array's device address is
 // looked up once per device (hipGetSymbolAddress, with that device current)
 // and only that pointer is handed to kernels.  Every call on a device shares
@@ -51,13 +52,20 @@ hipError_t launch_fit_queue_static(const shape_batch& b, const KOpts& o, const f
                                    const float* rec, const QCfg& cfg, float* p_out, float* chi2,
                                    float* perr, int32_t* iters, uint32_t* status,
                                    int32_t* sweeps, hipStream_t stream) {
+  // One wave per stamp: the fused fit gives the queue's results bit for bit
+  // and keeps its LM state in LDS, so it needs no workspace at all, and one
+  // launch per model takes the place of the start pass and of max_iter_lm
+  // steps of three to five launches each (2,000 stamps of sides 16 to 128:
+  // 4.3 ms of steps, most of them for the few stamps still active).
+  if (cfg.team == 1)
+    return launch_fit(b, o, p_init, rec, p_out, chi2, perr, iters, status, sweeps, stream);
+  // Teams: the drain pass finishes every stamp in one persistent launch per
+  // model, with the steps' results.
   void* ws = nullptr;
   hipError_t e = scratch_ptr(&ws);
   if (e != hipSuccess) return e;
   e = launch_queue_start(b, o, ws, p_init, rec, cfg, stream);
-  // every step of the cap: a step finds the stamps that are done and skips them
-  for (int k = 0; e == hipSuccess && k < o.max_iter_lm; ++k)
-    e = launch_queue_step(b, o, ws, cfg, stream);
+  if (e == hipSuccess) e = launch_queue_drain(b, o, ws, cfg, stream);
   if (e == hipSuccess)
     e = launch_queue_finish(b, o, ws, p_out, chi2, perr, iters, status, sweeps, stream);
   return e;
