@@ -670,6 +670,24 @@ __device__ __forceinline__ void centroid_any(const shape_batch& b, const KOpts& 
   if (t == 0) write_record(out, x, y, sigw, r50, sky0, (double)F / fp.fix, it, stt, iters, status, s);
 }
 
+// One stamp by the form that takes its side, at its slot class.
+template <int DT, int TEAM>
+__device__ __forceinline__ void centroid_form(const shape_batch& b, const KOpts& o,
+                                              const Stamp& st, int64_t s, float* rec,
+                                              int32_t* iters, uint32_t* status,
+                                              AnyShared<TEAM>& sh, int& parity) {
+  if constexpr (TEAM > 1) {
+    centroid_any<DT, TEAM, 64>(b, o, st, s, rec, iters, status, sh, parity);
+  } else {
+    switch (slot_class(SlotMap<TEAM>(st.side, 0).rows)) {
+      case 8: centroid_any<DT, TEAM, 8>(b, o, st, s, rec, iters, status, sh, parity); break;
+      case 16: centroid_any<DT, TEAM, 16>(b, o, st, s, rec, iters, status, sh, parity); break;
+      case 32: centroid_any<DT, TEAM, 32>(b, o, st, s, rec, iters, status, sh, parity); break;
+      default: centroid_any<DT, TEAM, 64>(b, o, st, s, rec, iters, status, sh, parity);
+    }
+  }
+}
+
 // One form per team size (team_takes: one wave up to side 64, three waves
 // for 65..96, four for 97..128); each skips the others' stamps.  Stamps that
 // cannot be processed are reported by the one-wave form, or by a team form
@@ -691,16 +709,37 @@ centroid_any_kernel(shape_batch b, KOpts o, float* rec, int32_t* iters, uint32_t
       write_failed(rec + s * SHAPE_REC_LEN, threadIdx.x, iters, status, s, st.bad);
       continue;
     }
-    if constexpr (TEAM > 1) {
-      centroid_any<DT, TEAM, 64>(b, o, st, s, rec, iters, status, sh, parity);
-    } else {
-      switch (slot_class(SlotMap<TEAM>(st.side, 0).rows)) {
-        case 8: centroid_any<DT, TEAM, 8>(b, o, st, s, rec, iters, status, sh, parity); break;
-        case 16: centroid_any<DT, TEAM, 16>(b, o, st, s, rec, iters, status, sh, parity); break;
-        case 32: centroid_any<DT, TEAM, 32>(b, o, st, s, rec, iters, status, sh, parity); break;
-        default: centroid_any<DT, TEAM, 64>(b, o, st, s, rec, iters, status, sh, parity);
-      }
-    }
+    centroid_form<DT, TEAM>(b, o, st, s, rec, iters, status, sh, parity);
+  }
+}
+
+// Every form in one launch, for a batch of mixed sides that does not fill the
+// card (kOneLaunch): workgroup s takes stamp s.  Bound by the slowest stamp's
+// iterations; three launches ran one after the other.
+template <int DT>
+__global__ __launch_bounds__(4 * kWave, SHAPE_CENTROID_ANY_WAVES_PER_SIMD) void
+centroid_mixed_kernel(shape_batch b, KOpts o, float* rec, int32_t* iters, uint32_t* status) {
+  __shared__ union Forms {
+    AnyShared<1> f1;
+    AnyShared<3> f3;
+    AnyShared<4> f4;
+    __device__ Forms() {}
+  } sh;
+  const int64_t s = blockIdx.x;   // the grid is b.n
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const Stamp st = stamp_info(b, s);
+  if (st.bad) {
+    write_failed(rec + s * SHAPE_REC_LEN, threadIdx.x, iters, status, s, st.bad);
+    return;
+  }
+  int parity = 0;
+  // a wave that ends here counts as arrived at every later barrier
+  if (team_takes<1>(st.side)) {
+    if (w < 1) centroid_form<DT, 1>(b, o, st, s, rec, iters, status, sh.f1, parity);
+  } else if (team_takes<3>(st.side)) {
+    if (w < 3) centroid_form<DT, 3>(b, o, st, s, rec, iters, status, sh.f3, parity);
+  } else {
+    centroid_form<DT, 4>(b, o, st, s, rec, iters, status, sh.f4, parity);
   }
 }
 
@@ -728,6 +767,11 @@ void launch_dtype(const shape_batch& b, const KOpts& o, float* rec, int32_t* ite
   // workgroup.  Mixed sides: every form, each workgroup looking at a chunk of
   // stamps and taking those of its form.
   const bool mixed = b.side != nullptr;
+  if (mixed && b.n <= kOneLaunch) {
+    hipLaunchKernelGGL((centroid_mixed_kernel<DT>), dim3((unsigned)b.n), dim3(4 * kWave), 0, stream,
+                       b, o, rec, iters, status);
+    return;
+  }
   const bool f1 = mixed || team_takes<1>(b.side0) ||
                   (!team_takes<3>(b.side0) && !team_takes<4>(b.side0));
   const bool f3 = mixed || team_takes<3>(b.side0), f4 = mixed || team_takes<4>(b.side0);
@@ -736,15 +780,15 @@ void launch_dtype(const shape_batch& b, const KOpts& o, float* rec, int32_t* ite
     return dim3((unsigned)(g < cap ? g : cap));
   };
   if (f1) {
-    const int c = mixed ? chunk_of<1>() : 1;
+    const int c = mixed ? chunk_of<1>(b.n) : 1;
     hipLaunchKernelGGL((centroid_any_kernel<DT, 1>), grid(c), dim3(kWave), 0, stream, b, o, rec, iters, status, 1, c);
   }
   if (f3) {
-    const int c = mixed ? chunk_of<3>() : 1;
+    const int c = mixed ? chunk_of<3>(b.n) : 1;
     hipLaunchKernelGGL((centroid_any_kernel<DT, 3>), grid(c), dim3(3 * kWave), 0, stream, b, o, rec, iters, status, f1 ? 0 : 1, c);
   }
   if (f4) {
-    const int c = mixed ? chunk_of<4>() : 1;
+    const int c = mixed ? chunk_of<4>(b.n) : 1;
     hipLaunchKernelGGL((centroid_any_kernel<DT, 4>), grid(c), dim3(4 * kWave), 0, stream, b, o, rec, iters, status, f1 ? 0 : 1, c);
   }
 }

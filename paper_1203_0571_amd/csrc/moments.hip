@@ -505,6 +505,24 @@ __device__ __forceinline__ void moments_any(const shape_batch& b, const KOpts& o
   if (t == 0) write_out(out, r_in, z, size, it, iters, status, s);
 }
 
+// One stamp by the form that takes its side, at its slot class.
+template <int DT, int TEAM>
+__device__ __forceinline__ void moments_form(const shape_batch& b, const KOpts& o, const Stamp& st,
+                                             int64_t s, const float (&r_in)[SHAPE_REC_LEN],
+                                             float* out, int32_t* iters, uint32_t* status,
+                                             double* part, StepShare* share, int& parity) {
+  if constexpr (TEAM > 1) {
+    moments_any<DT, TEAM, 64>(b, o, st, s, r_in, out, iters, status, part, share, parity);
+  } else {
+    switch (slot_class(SlotMap<TEAM>(st.side, 0).rows)) {
+      case 8: moments_any<DT, TEAM, 8>(b, o, st, s, r_in, out, iters, status, part, share, parity); break;
+      case 16: moments_any<DT, TEAM, 16>(b, o, st, s, r_in, out, iters, status, part, share, parity); break;
+      case 32: moments_any<DT, TEAM, 32>(b, o, st, s, r_in, out, iters, status, part, share, parity); break;
+      default: moments_any<DT, TEAM, 64>(b, o, st, s, r_in, out, iters, status, part, share, parity);
+    }
+  }
+}
+
 // One form per team size (team_takes: one wave up to side 64, three waves
 // for 65..96, four for 97..128); each skips the others' stamps.  Stamps that
 // cannot be processed are reported by the one-wave form, or by a team form
@@ -536,16 +554,42 @@ moments_any_kernel(shape_batch b, KOpts o, const float* rec_in, float* rec_out, 
       }
       continue;
     }
-    if constexpr (TEAM > 1) {
-      moments_any<DT, TEAM, 64>(b, o, st, s, r_in, out, iters, status, part, share, parity);
-    } else {
-      switch (slot_class(SlotMap<TEAM>(st.side, 0).rows)) {
-        case 8: moments_any<DT, TEAM, 8>(b, o, st, s, r_in, out, iters, status, part, share, parity); break;
-        case 16: moments_any<DT, TEAM, 16>(b, o, st, s, r_in, out, iters, status, part, share, parity); break;
-        case 32: moments_any<DT, TEAM, 32>(b, o, st, s, r_in, out, iters, status, part, share, parity); break;
-        default: moments_any<DT, TEAM, 64>(b, o, st, s, r_in, out, iters, status, part, share, parity);
-      }
+    moments_form<DT, TEAM>(b, o, st, s, r_in, out, iters, status, part, share, parity);
+  }
+}
+
+// Every form in one launch, for a batch of mixed sides that does not fill the
+// card (as centroid_mixed_kernel): workgroup s takes stamp s.
+template <int DT>
+__global__ __launch_bounds__(4 * kWave, SHAPE_MOMENTS_ANY_WAVES_PER_SIMD) void
+moments_mixed_kernel(shape_batch b, KOpts o, const float* rec_in, float* rec_out, int32_t* iters,
+                     uint32_t* status) {
+  __shared__ double part[2 * 4 * 12];
+  __shared__ StepShare share[2];
+  const int64_t s = blockIdx.x;   // the grid is b.n
+  const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWave);
+  const Stamp st = stamp_info(b, s);
+  float* out = rec_out + s * SHAPE_REC_LEN;
+  float r_in[SHAPE_REC_LEN];
+  const bool rec_ok = read_record(rec_in + s * SHAPE_REC_LEN, r_in);
+  if (st.bad || !rec_ok) {
+    __syncthreads();
+    if (t < SHAPE_REC_LEN) out[t] = qnan();
+    if (t == 0) {
+      iters[s] = 0;
+      status[s] = st.bad ? st.bad : SHAPE_ST_BAD_INPUT;
     }
+    return;
+  }
+  int parity = 0;
+  // a wave that ends here counts as arrived at every later barrier (the
+  // team's first one follows its own read of the input record)
+  if (team_takes<1>(st.side)) {
+    if (w < 1) moments_form<DT, 1>(b, o, st, s, r_in, out, iters, status, part, share, parity);
+  } else if (team_takes<3>(st.side)) {
+    if (w < 3) moments_form<DT, 3>(b, o, st, s, r_in, out, iters, status, part, share, parity);
+  } else {
+    moments_form<DT, 4>(b, o, st, s, r_in, out, iters, status, part, share, parity);
   }
 }
 
@@ -573,6 +617,11 @@ void launch_dtype(const shape_batch& b, const KOpts& o, const float* rec_in, flo
   // workgroup.  Mixed sides: every form, each workgroup looking at a chunk of
   // stamps and taking those of its form.
   const bool mixed = b.side != nullptr;
+  if (mixed && b.n <= kOneLaunch) {
+    hipLaunchKernelGGL((moments_mixed_kernel<DT>), dim3((unsigned)b.n), dim3(4 * kWave), 0, stream,
+                       b, o, rec_in, rec_out, iters, status);
+    return;
+  }
   const bool f1 = mixed || team_takes<1>(b.side0) ||
                   (!team_takes<3>(b.side0) && !team_takes<4>(b.side0));
   const bool f3 = mixed || team_takes<3>(b.side0), f4 = mixed || team_takes<4>(b.side0);
@@ -581,15 +630,15 @@ void launch_dtype(const shape_batch& b, const KOpts& o, const float* rec_in, flo
     return dim3((unsigned)(g < cap ? g : cap));
   };
   if (f1) {
-    const int c = mixed ? chunk_of<1>() : 1;
+    const int c = mixed ? chunk_of<1>(b.n) : 1;
     hipLaunchKernelGGL((moments_any_kernel<DT, 1>), grid(c), dim3(kWave), 0, stream, b, o, rec_in, rec_out, iters, status, 1, c);
   }
   if (f3) {
-    const int c = mixed ? chunk_of<3>() : 1;
+    const int c = mixed ? chunk_of<3>(b.n) : 1;
     hipLaunchKernelGGL((moments_any_kernel<DT, 3>), grid(c), dim3(3 * kWave), 0, stream, b, o, rec_in, rec_out, iters, status, f1 ? 0 : 1, c);
   }
   if (f4) {
-    const int c = mixed ? chunk_of<4>() : 1;
+    const int c = mixed ? chunk_of<4>(b.n) : 1;
     hipLaunchKernelGGL((moments_any_kernel<DT, 4>), grid(c), dim3(4 * kWave), 0, stream, b, o, rec_in, rec_out, iters, status, f1 ? 0 : 1, c);
   }
 }
