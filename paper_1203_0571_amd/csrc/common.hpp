@@ -260,6 +260,15 @@ __device__ __forceinline__ float load_rel(const void* sp, uint32_t k, float scal
   }
 }
 
+// The same as stored (FP16: before the scale).
+template <int DT>
+__device__ __forceinline__ float load_raw(const void* sp, uint32_t k) {
+  if constexpr (DT == SHAPE_F32)
+    return static_cast<const float*>(sp)[k];
+  else
+    return static_cast<float>(static_cast<const _Float16*>(sp)[k]);
+}
+
 template <int DT>
 __device__ __forceinline__ const void* stamp_base(const shape_batch& b, const Stamp& st) {
   if constexpr (DT == SHAPE_F32)

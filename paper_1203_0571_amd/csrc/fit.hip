@@ -133,6 +133,8 @@ hipError_t launch_fit_dt(const shape_batch& b, const KOpts& o, const float* p_in
 hipError_t launch_fit(const shape_batch& b, const KOpts& o, const float* p_init, const float* rec,
                       float* p_out, float* chi2, float* perr, int32_t* iters, uint32_t* status,
                       int32_t* sweeps, hipStream_t stream) {
+  if (fit_takes_split(b))
+    return launch_fit_split(b, o, p_init, rec, p_out, chi2, perr, iters, status, sweeps, stream);
   if (b.dtype == SHAPE_F32)
     return launch_fit_dt<SHAPE_F32>(b, o, p_init, rec, p_out, chi2, perr, iters, status, sweeps,
                                     stream);

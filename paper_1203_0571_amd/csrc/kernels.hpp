@@ -14,6 +14,12 @@ hipError_t launch_moments(const shape_batch& b, const KOpts& o, const float* rec
 hipError_t launch_fit(const shape_batch& b, const KOpts& o, const float* p_init, const float* rec,
                       float* p_out, float* chi2, float* perr, int32_t* iters, uint32_t* status,
                       int32_t* sweeps, hipStream_t stream);
+// The same results with four waves per stamp, for the batches fit_takes_split
+// names (launch_fit calls it).
+bool fit_takes_split(const shape_batch& b);
+hipError_t launch_fit_split(const shape_batch& b, const KOpts& o, const float* p_init,
+                            const float* rec, float* p_out, float* chi2, float* perr,
+                            int32_t* iters, uint32_t* status, int32_t* sweeps, hipStream_t stream);
 
 // Work-queue configuration (see shape_queue_cfg in shape.h).
 struct QCfg {

@@ -18,6 +18,7 @@
 // solve in one thread), from the reduced sums kept in LDS.
 #pragma once
 
+#include "split_sweep.hpp"
 #include "sweep.hpp"
 
 namespace shape {
@@ -52,6 +53,9 @@ struct LmShared {
   double M[21];  // damped Schur complement, lower triangle row by row
   int cur;       // which of sums[] holds the current point
 };
+
+// A "team" of kSplitWaves waves that forms the one-wave sums (split_sweep).
+constexpr int kSplit = 0;
 
 template <int TEAM>
 __device__ __forceinline__ void team_sync();
@@ -120,30 +124,37 @@ __device__ __forceinline__ void team_sync() {
 // One sweep at trial t; the team's reduced sums are left in S (kSums doubles,
 // entry k at S[k * stride]: LDS for the fused fit, the stamp's column of the
 // workspace for the batched form).  xs is LDS scratch of TEAM * kSums doubles
-// for the cross-wave combination (unused for TEAM == 1).  tid = thread index
+// for the cross-wave combination (unused for TEAM == 1).  TEAM == kSplit: a
+// workgroup of kSplitWaves waves with the one-wave sums (split_sweep).  tid = thread index
 // within the team; stage: the LDS buffer of kLayoutStaged (kStageBytes).
 template <int DT, int MODEL, uint32_t EM, int TEAM, int LAYOUT = kLayoutAny>
 __device__ __forceinline__ void sweep_sums(const shape_batch& b, const Stamp& st, const TrialF& t,
                                            double* S, double* xs, int tid, int64_t stride = 1,
                                            void* stage = nullptr) {
-  Acc<EM> acc;
-  sweep<DT, MODEL, EM, kWave * TEAM, float, LAYOUT>(b, st, t, acc, tid, stage);
   const int lane = tid & (kWave - 1);
-  team_sync<TEAM>();  // previous readers of S / xs are done
-  if constexpr (TEAM == 1) {
-    reduce_store<EM>(acc, S, lane, stride);
+  if constexpr (TEAM == kSplit) {
+    team_sync<TEAM>();  // previous readers of S are done
+    split_sweep<DT, MODEL, EM, LAYOUT>(b, st, t, S, tid);
+    team_sync<TEAM>();
   } else {
-    reduce_store<EM>(acc, xs + (tid / kWave) * kSums, lane);
-  }
-  team_sync<TEAM>();
-  if constexpr (TEAM > 1) {
-    if (tid < kSums) {
-      double v = xs[tid];
-#pragma unroll
-      for (int w = 1; w < TEAM; ++w) v += xs[w * kSums + tid];
-      S[tid * stride] = v;
+    Acc<EM> acc;
+    sweep<DT, MODEL, EM, kWave * TEAM, float, LAYOUT>(b, st, t, acc, tid, stage);
+    team_sync<TEAM>();  // previous readers of S / xs are done
+    if constexpr (TEAM == 1) {
+      reduce_store<EM>(acc, S, lane, stride);
+    } else {
+      reduce_store<EM>(acc, xs + (tid / kWave) * kSums, lane);
     }
     team_sync<TEAM>();
+    if constexpr (TEAM > 1) {
+      if (tid < kSums) {
+        double v = xs[tid];
+#pragma unroll
+        for (int w = 1; w < TEAM; ++w) v += xs[w * kSums + tid];
+        S[tid * stride] = v;
+      }
+      team_sync<TEAM>();
+    }
   }
   if (tid == 0) S[sa(7, 7) * stride] = (double)st.npix;
   team_sync<TEAM>();
@@ -204,13 +215,49 @@ __device__ __forceinline__ void amp_apply(double* S, const AmpStep& r, double I0
   if constexpr (has(LIN, 7)) S[sg(7)] = 0.0;
 }
 
+// The same by one wave, a sum per lane (entries of parameters that are not
+// fitted are rewritten too, and read by nobody): where one thread's LDS reads
+// and writes wait for each other, about 1,500 cycles.  For a stamp's latency
+// only: in the one-wave fit of large batches the extra registers and barriers
+// cost more than the serial instructions (fit 18.63 against 18.35 ms on 262,144
+// stamps of 64 x 64).
+template <uint32_t LIN>
+__device__ __forceinline__ void amp_apply_lanes(double* S, const AmpStep& r, double I0, int lane) {
+  const double sc = (I0 + r.d6) * rcp_f64(I0);
+  // entry `lane`: 0 chi^2, 1 + k (J^T r)_k, 9 + tri(k, l)
+  const int q = lane - 9;
+  const int k = q < 0 ? lane - 1
+                      : (q >= 8) + (q >= 15) + (q >= 21) + (q >= 26) + (q >= 30) + (q >= 33) + (q >= 35);
+  const int l = q < 0 ? 6 : q - tri(k, k) + k;
+  double v = 0.0;
+  if (lane < kSums) {
+    v = S[lane];
+    if (lane == 0) {
+      v = v - fma(S[sg(6)], r.d6, S[sg(7)] * r.d7);
+    } else if (q < 0) {
+      if (k < 6)
+        v = sc * fma(-r.d7, S[sa(k, 7)], fma(-r.d6, S[sa(k, 6)], v));
+      else if ((k == 6 && has(LIN, 6)) || (k == 7 && has(LIN, 7)))
+        v = 0.0;
+    } else if (k < 6) {
+      v = l < 6 ? v * (sc * sc) : v * sc;
+    }
+  }
+  wave_sync();   // every lane has read what the others rewrite
+  if (lane < kSums) S[lane] = v;
+}
+
 // The team form: every thread solves, thread 0 rewrites S (in LDS).
 template <uint32_t EM, uint32_t LIN, int TEAM>
 __device__ __forceinline__ AmpStep profile_amplitudes(double* S, double I0, int tid) {
   const AmpStep r = amp_solve<LIN>(S);
   if (!r.ok) return r;
   team_sync<TEAM>();
-  if (tid == 0) amp_apply<EM, LIN>(S, r, I0);
+  if constexpr (TEAM == kSplit) {
+    if (tid < kWave) amp_apply_lanes<LIN>(S, r, I0, tid);
+  } else {
+    if (tid == 0) amp_apply<EM, LIN>(S, r, I0);
+  }
   team_sync<TEAM>();
   return r;
 }
@@ -510,12 +557,14 @@ __device__ __forceinline__ void lm_iterate(const shape_batch& b, const KOpts& o,
   constexpr int NT = NN * (NN + 1) / 2;
   if (tid < NT) {
     const double* C = W.sums[cur];
-    int a = 0, c = tid;
-    while (c > a) {
-      c -= a + 1;
-      ++a;
-    }
-    double v = schur_entry<LIN>(C, nth_bit(NL, a), nth_bit(NL, c));
+    // row and column of entry tid: the parameters of a mask are consecutive
+    static_assert(((NL >> __builtin_ctz(NL)) & ((NL >> __builtin_ctz(NL)) + 1)) == 0, "a run of bits");
+    int a = 0;
+#pragma unroll
+    for (int r = 1; r < NN; ++r) a += tid >= r * (r + 1) / 2;
+    const int c = tid - a * (a + 1) / 2;
+    constexpr int k0 = __builtin_ctz(NL);
+    double v = schur_entry<LIN>(C, k0 + a, k0 + c);
     if (a == c) v *= 1.0 + W.L.lambda;
     W.M[tid] = v;
   }

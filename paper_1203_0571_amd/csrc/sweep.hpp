@@ -267,6 +267,252 @@ __device__ __forceinline__ Trial<T> make_trial(const double* p, int model, doubl
   return t;
 }
 
+// acc + xy where xy = x y: rounded once (FUSED) or with xy rounded first.
+// The sums of whole columns take one or the other by layout, spelled out so
+// that every kernel that forms them gets the same bits however its compiler
+// arranges the loop.
+template <bool FUSED, typename T>
+__device__ __forceinline__ T add_product(T x, T y, T xy, T acc) {
+  if constexpr (FUSED) {
+    return Arith<T>::fma(x, y, acc);
+  } else {
+#pragma clang fp contract(off)
+    return acc + xy;
+  }
+}
+
+// A rendered pixel as the sums take it: m0 the profile at unit amplitude,
+// h the common factor of the x0, y0, e1, e2 columns, r the residual;
+// Sersic: c = m0 t, q5 = L k5a + k5b (dm/dn = c q5); Moffat: cR = c R^2
+// (dm/drd = cR k4), q5 = log2(base).  Fields a caller does not use cost
+// nothing.
+template <typename T>
+struct Px {
+  T m0, h, c, t, q5, cR, r;
+};
+
+// The FP32 Sersic instance applies the constant factors k7 (of the x0, y0,
+// e1, e2 columns) and k4 (of the Re column) to the sums once, after the sweep.
+template <typename T, int MODEL>
+__host__ __device__ constexpr bool fold_factors() {
+  return sizeof(T) == 4 && MODEL == SHAPE_SERSIC;
+}
+
+// The residual of a pixel stored as `raw`.  FP16 storage in the FP32
+// instance: one rounding for the scale and the difference together.
+template <int DT, typename T>
+__device__ __forceinline__ T residual(float raw, float scale, T m) {
+  if constexpr (DT == SHAPE_F32)
+    return (T)raw - m;
+  else if constexpr (sizeof(T) == 4)
+    return fmaf(raw, scale, -m);
+  else
+    return (T)(raw * scale) - m;
+}
+
+// Renders a pixel stored as `raw` at R^2 = R2 (unfloored).
+template <int DT, int MODEL, uint32_t EM, typename T>
+__device__ __forceinline__ Px<T> render(const Trial<T>& t, float raw, float scale, T R2) {
+  using A = Arith<T>;
+  Px<T> p;
+  const bool floored = R2 < A::kR2Floor;
+  R2 = floored ? A::kR2Floor : R2;
+  if constexpr (MODEL == SHAPE_SERSIC) {
+    const T L = A::lg2(R2);
+    p.t = A::ex2(A::fma(L, t.ha, t.hc));
+    p.m0 = A::ex2(t.nb2 * p.t);
+    p.c = p.m0 * p.t;
+    if constexpr (fold_factors<T, MODEL>())
+      p.h = p.c * A::rcp(R2);
+    else
+      p.h = p.c * A::rcp(R2) * t.k7;
+    if constexpr (has(EM, 5)) p.q5 = A::fma(L, t.k5a, t.k5b);
+  } else {
+    const T base = A::fma(R2, t.irdsq, (T)1);
+    const T lb = A::lg2(base);
+    p.m0 = A::ex2(-t.beta * lb);
+    p.c = p.m0 * A::rcp(base);
+    p.h = p.c * t.k7;
+    p.cR = p.c * R2;
+    p.q5 = lb;
+  }
+  p.h = floored ? (T)0 : p.h;
+  p.r = residual<DT>(raw, scale, A::fma(t.I0, p.m0, t.sky));
+  return p;
+}
+
+// The moment form's constants of a sweep.  The FP32 instance takes R^2 in
+// units of Re^2, s = R^2 S with S = 1 / Re^2 (2^(hc / ha)): then
+// t = 2^(ha log2 s) needs no added constant, and t / R^2 = S 2^((ha - 1) log2
+// s) gives h without a reciprocal (one transcendental fewer per pixel; S goes
+// into the folded factor of the x0, y0, e1, e2 columns, log2 S into the n
+// column's constant).
+template <typename T>
+struct MomentUnits {
+  T S = (T)1, floor = Arith<T>::kR2Floor, ham1 = (T)0, k5b = (T)0;
+  __device__ __forceinline__ MomentUnits() {}
+  __device__ __forceinline__ explicit MomentUnits(const Trial<T>& t) {
+    if constexpr (sizeof(T) == 4) {
+      using A = Arith<T>;
+      const T lS = A::uni(t.hc * A::rcp(t.ha));
+      S = A::uni(A::ex2(lS));
+      floor = A::uni(A::kR2Floor * S);
+      ham1 = A::uni(t.ha - (T)1);
+      k5b = A::uni(A::fma(-lS, t.k5a, t.k5b));
+    }
+  }
+};
+
+// Renders a Sersic pixel stored as `raw` at s = R^2 S.  The FP64 instance (the
+// adjoint's; its exp2 costs more than its reciprocal) renders as render()
+// does, with the factors k7 and k4 in the columns.
+template <int DT, uint32_t EM, typename T>
+__device__ __forceinline__ Px<T> render_moment(const Trial<T>& t, const MomentUnits<T>& mu,
+                                               float raw, float scale, T s2) {
+  using A = Arith<T>;
+  Px<T> p;
+  const bool floored = s2 < mu.floor;
+  s2 = floored ? mu.floor : s2;
+  const T L = A::lg2(s2);
+  if constexpr (sizeof(T) == 4) {
+    const T tr = A::ex2(L * mu.ham1);   // t / s
+    p.t = tr * s2;
+    p.m0 = A::ex2(t.nb2 * p.t);
+    p.c = p.m0 * p.t;
+    p.h = p.m0 * tr;                    // h / S
+  } else {
+    p.t = A::ex2(A::fma(L, t.ha, t.hc));
+    p.m0 = A::ex2(t.nb2 * p.t);
+    p.c = p.m0 * p.t;
+    p.h = p.c * A::rcp(s2) * t.k7;
+  }
+  p.h = floored ? (T)0 : p.h;
+  if constexpr (has(EM, 5)) p.q5 = A::fma(L, t.k5a, sizeof(T) == 4 ? mu.k5b : t.k5b);
+  p.r = residual<DT>(raw, scale, A::fma(t.I0, p.m0, t.sky));
+  return p;
+}
+
+// A pixel column of a stamp (u1 fixed): the per-column coefficients of R^2,
+// of N u and of the e-derivative factors P2 = e1 R^2 + w_1, P3 = e2 R^2 + w_2,
+// and their values at u2.
+template <typename T>
+struct Column {
+  T qb, qc, p2b, p2c, p3b, p3c, c3, c4;
+  __device__ __forceinline__ Column(const Trial<T>& t, const T u1) {
+    using A = Arith<T>;
+    const T uu = u1 * u1;
+    qb = t.qb1 * u1;
+    qc = t.qc2 * uu;
+    p2b = t.e1 * qb;
+    p2c = A::fma(t.e1, qc, -t.a11 * uu);
+    p3b = A::fma(t.e2, qb, (T)-2 * u1);
+    p3c = A::fma(t.e2, qc, -t.a12 * uu);
+    c3 = t.n11 * u1;
+    c4 = t.n12 * u1;
+  }
+  using A = Arith<T>;
+  __device__ __forceinline__ T R2(const Trial<T>& t, T u2) const { return A::fma(A::fma(t.qa, u2, qb), u2, qc); }
+  __device__ __forceinline__ T n1(const Trial<T>& t, T u2) const { return A::fma(t.n12, u2, c3); }
+  __device__ __forceinline__ T n2(const Trial<T>& t, T u2) const { return A::fma(t.n22, u2, c4); }
+  __device__ __forceinline__ T P2(const Trial<T>& t, T u2) const { return A::fma(A::fma(t.p2a, u2, p2b), u2, p2c); }
+  __device__ __forceinline__ T P3(const Trial<T>& t, T u2) const { return A::fma(A::fma(t.p3a, u2, p3b), u2, p3c); }
+};
+
+// The same at a pixel on its own, (v1, v2) = S(e) u.
+template <typename T>
+struct Walk {
+  T R2, n1, n2, P2, P3;
+  __device__ __forceinline__ Walk(const Trial<T>& t, const T u1, const T u2) {
+    using A = Arith<T>;
+    const T v1 = A::fma(t.a11, u1, t.a12 * u2), v2 = A::fma(t.a12, u1, t.a22 * u2);
+    R2 = A::fma(v1, v1, v2 * v2) * t.invD;
+    n1 = A::fma(t.n11, u1, t.n12 * u2);
+    n2 = A::fma(t.n12, u1, t.n22 * u2);
+    P2 = A::fma(t.e1, R2, A::fma(v2, u2, -v1 * u1));
+    P3 = A::fma(t.e2, R2, -A::fma(v1, u2, v2 * u1));
+  }
+};
+
+// A lane's moment sums (see sweep's kMom): M_s = sum h^2 u2^s, X_vj = sum H_j
+// J_v for the Re, n and I0 columns, Y_j = sum H_j, g_j = sum H_j r.
+template <typename T>
+struct Moments {
+  T M[5] = {}, X[3][3] = {}, Y[3] = {};
+  double g[3] = {};
+};
+
+// The column sums from a lane's moments, in FP64: column k is
+// h sum_j C[k][j] u2^j (degree 1 for x0, y0, 2 for e1, e2).  Forms J^T r
+// (GR), the sky column's sums (GY), those against Re, n and I0 (GX) and the
+// four columns' own (GM).  The FP32 instance folds the factor k7 S of these
+// columns (and k4 of the Re column) in here, not into the sums afterwards.
+template <uint32_t EM, bool JTJ, bool GR, bool GY, bool GX, bool GM, typename T>
+__device__ __forceinline__ void recombine(const Trial<T>& t, const MomentUnits<T>& mu,
+                                          const Column<T>& col, const Moments<T>& m,
+                                          Acc<EM, T>& acc) {
+  constexpr bool kF32 = sizeof(T) == 4;
+  const double f7 = kF32 ? (double)(t.k7 * mu.S) : 1.0;
+  const double f4 = kF32 ? (double)t.k4 : 1.0;
+  const double C[4][3] = {{col.c3 * f7, t.n12 * f7, 0.0},
+                          {col.c4 * f7, t.n22 * f7, 0.0},
+                          {col.p2c * f7, col.p2b * f7, t.p2a * f7},
+                          {col.p3c * f7, col.p3b * f7, t.p3a * f7}};
+  double M[5], X[3][3], Y[3];
+#pragma unroll
+  for (int s = 0; s < 5; ++s) M[s] = (double)m.M[s];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    Y[j] = (double)m.Y[j];
+#pragma unroll
+    for (int v = 0; v < 3; ++v) X[v][j] = (double)m.X[v][j] * (v == 0 ? f4 : 1.0);
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const int da = a < 2 ? 2 : 3;   // coefficients of column a
+    double g = 0.0, y = 0.0, x[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = 0; j < da; ++j) {
+      g = fma(C[a][j], m.g[j], g);
+      y = fma(C[a][j], Y[j], y);
+#pragma unroll
+      for (int v = 0; v < 3; ++v) x[v] = fma(C[a][j], X[v][j], x[v]);
+    }
+    if constexpr (GR) acc.g[a] = g;
+    if constexpr (JTJ) {
+      if (GY && has(EM, 7)) acc.A[tri(a, 7)] = (T)y;
+#pragma unroll
+      for (int v = 0; v < 3; ++v)
+        if (GX && has(EM, 4 + v)) acc.A[tri(a, 4 + v)] = (T)x[v];
+    }
+  }
+  // P[c][i] = sum_j C[c][j] M[i + j]; entry (a, c) = sum_i C[a][i] P[c][i]
+  if constexpr (JTJ && GM) {
+    double P[4][3];
+#pragma unroll
+    for (int c2 = 0; c2 < 4; ++c2) {
+      const int dc = c2 < 2 ? 2 : 3;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        double q = 0.0;
+#pragma unroll
+        for (int j = 0; j < dc; ++j) q = fma(C[c2][j], M[i + j], q);
+        P[c2][i] = q;
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      const int da = a < 2 ? 2 : 3;
+#pragma unroll
+      for (int c2 = a; c2 < 4; ++c2) {
+        double q = 0.0;
+#pragma unroll
+        for (int i = 0; i < da; ++i) q = fma(C[a][i], P[c2][i], q);
+        acc.A[tri(a, c2)] = (T)q;
+      }
+    }
+  }
+}
+
 // One sweep: model, residual, Jacobian columns in EM, and their sums.
 // Pixel layouts of a sweep: kLayoutAny walks any side with the lane stride;
 // kLayoutRows is for a wave alone on a stamp whose side divides 64 with at
@@ -327,14 +573,33 @@ inline int single_wave_layout(const shape_batch& b, int model) {
 #define SHAPE_SWEEP_FLUSH 8
 #endif
 
+// Whether a sweep over a stamp of side `side` adds the columns' own sums with
+// one rounding (add_product): the FP32 instance of each layout.
+template <int DT, int LAYOUT>
+__host__ __device__ constexpr bool sums_fused(int side, bool moments) {
+  if (LAYOUT == kLayoutRows)
+    return (moments || DT == SHAPE_F32) && side * side / kWave % 8 == 0;
+  return (LAYOUT == kLayoutSegs || LAYOUT == kLayoutSegsStaged) && side >= kSegsMinSide;
+}
+
+// The kinds of sums a sweep forms: J^T J of (x0, y0, e1, e2) among themselves;
+// of those against (size, n, I0); of (size, n, I0) among themselves and all
+// sums of the sky column; chi^2 and J^T r.
+constexpr uint32_t kSumsShape = 1u, kSumsCross = 2u, kSumsProfile = 4u, kSumsGradient = 8u;
+constexpr uint32_t kSumsAll = 15u;
+__host__ __device__ constexpr bool in_sums(uint32_t sums, int k, int l) {   // k <= l
+  return (sums & (l == 7 || k >= 4 ? kSumsProfile : l >= 4 ? kSumsCross : kSumsShape)) != 0u;
+}
+
 // JTJ = false leaves the J^T J sums at zero (callers that need only chi^2
-// and J^T r).
+// and J^T r); SUMS: the kinds of sums formed (the others are left at zero).
 template <int DT, int MODEL, uint32_t EM, int STRIDE = kWave, typename T = float,
-          int LAYOUT = kLayoutAny, bool JTJ = true>
+          int LAYOUT = kLayoutAny, bool JTJ = true, uint32_t SUMS = kSumsAll>
 __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, const Trial<T>& t,
                              Acc<EM, T>& acc, int tid = -1, void* stage = nullptr) {
   using A = Arith<T>;
   constexpr int kFlush = sizeof(T) == 4 ? SHAPE_SWEEP_FLUSH : 0;
+  constexpr bool kGrad = (SUMS & kSumsGradient) != 0u;   // chi^2 and J^T r
   acc.c2 = 0.0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) acc.g[k] = 0.0;
@@ -343,10 +608,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
   T c2p = (T)0, gp[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) gp[k] = (T)0;
-  // For the FP32 Sersic instance the constant factors k7 (of the x0, y0, e1,
-  // e2 columns) and k4 (of the Re column) are applied to the sums once, after
-  // the sweep.
-  constexpr bool kFold = sizeof(T) == 4 && MODEL == SHAPE_SERSIC;
+  constexpr bool kFold = fold_factors<T, MODEL>();
   // Moment form of the row layout (Sersic with x0, y0, e1, e2 free; the FP32
   // instance of the fit and the FP64 instance of the adjoint):
   // along a lane's column the four shape columns are h times polynomials in
@@ -358,20 +620,10 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
   // operations per pixel where the columns cost 40.
   constexpr bool kMom = MODEL == SHAPE_SERSIC && LAYOUT == kLayoutRows && (EM & 0xFu) == 0xFu &&
                         (sizeof(T) == 8 || JTJ);
-  constexpr int kMomN = kMom ? 3 : 1;
-  T mM[2 * kMomN - 1], mX[3][kMomN], mY[kMomN], gq[kMomN];
-  double gm[kMomN];
-#pragma unroll
-  for (int j = 0; j < kMomN; ++j) {
-    mY[j] = gq[j] = (T)0;
-    gm[j] = 0.0;
-#pragma unroll
-    for (int v = 0; v < 3; ++v) mX[v][j] = (T)0;
-  }
-#pragma unroll
-  for (int s = 0; s < 2 * kMomN - 1; ++s) mM[s] = (T)0;
+  Moments<T> mom;
+  T gq[3] = {(T)0, (T)0, (T)0};
   auto flush = [&]() {
-    if constexpr (kFlush > 0) {
+    if constexpr (kFlush > 0 && kGrad) {
       acc.c2 += (double)c2p;
       c2p = (T)0;
 #pragma unroll
@@ -382,48 +634,32 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
       }
       if constexpr (kMom) {
 #pragma unroll
-        for (int j = 0; j < kMomN; ++j) {
-          gm[j] += (double)gq[j];
+        for (int j = 0; j < 3; ++j) {
+          mom.g[j] += (double)gq[j];
           gq[j] = (T)0;
         }
       }
     }
   };
-  // Per pixel: d = data, R2 = R^2 (unfloored), (n1, n2) = N u and the
+  // Per pixel: d = data as stored, R2 = R^2 (unfloored), (n1, n2) = N u and the
   // e-derivative factors P2 = e1 R^2 + w_1, P3 = e2 R^2 + w_2.
   // first: the pixel opens a run of kFlush pixels, so its terms start the
   // FP32 partials instead of being added to them (the same values as adding
   // them to zeros; a compile-time constant where the runs are unrolled)
-  auto pixel = [&](const T d, T R2, const T n1, const T n2, const T P2, const T P3,
-                   const bool first = false) {
-    const bool floored = R2 < A::kR2Floor;
-    R2 = floored ? A::kR2Floor : R2;
+  // fused: how the columns' own sums round (add_product)
+  auto pixel = [&](auto fused, const float d, const T R2, const T n1, const T n2, const T P2,
+                   const T P3, const bool first = false) {
+    constexpr bool kFused = decltype(fused)::value;
+    const Px<T> px = render<DT, MODEL, EM>(t, d, st.scale, R2);
+    const T m0 = px.m0, h = px.h, r = px.r;
     T J[8];
-    T m0, h;
     if constexpr (MODEL == SHAPE_SERSIC) {
-      const T L = A::lg2(R2);
-      const T tt = A::ex2(A::fma(L, t.ha, t.hc));
-      m0 = A::ex2(t.nb2 * tt);
-      const T c = m0 * tt;
-      if constexpr (kFold) {
-        h = c * A::rcp(R2);
-        if constexpr (has(EM, 4)) J[4] = c;
-      } else {
-        h = c * A::rcp(R2) * t.k7;
-        if constexpr (has(EM, 4)) J[4] = c * t.k4;
-      }
-      if constexpr (has(EM, 5)) J[5] = c * A::fma(L, t.k5a, t.k5b);
+      if constexpr (has(EM, 4)) J[4] = kFold ? px.c : px.c * t.k4;
+      if constexpr (has(EM, 5)) J[5] = px.c * px.q5;
     } else {
-      const T base = A::fma(R2, t.irdsq, (T)1);
-      const T lb = A::lg2(base);
-      m0 = A::ex2(-t.beta * lb);
-      const T c = m0 * A::rcp(base);
-      h = c * t.k7;
-      if constexpr (has(EM, 4)) J[4] = c * R2 * t.k4;
-      if constexpr (has(EM, 5)) J[5] = m0 * lb * t.k5a;   // d/dbeta
+      if constexpr (has(EM, 4)) J[4] = px.cR * t.k4;
+      if constexpr (has(EM, 5)) J[5] = m0 * px.q5 * t.k5a;   // d/dbeta
     }
-    h = floored ? (T)0 : h;
-    const T r = d - A::fma(t.I0, m0, t.sky);
     if constexpr (has(EM, 0) || has(EM, 1)) {
       J[0] = h * n1;
       J[1] = h * n2;
@@ -434,6 +670,11 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     }
     J[6] = m0;
     J[7] = (T)1;
+    // J[a] = px_x[a] px_y[a] (x 1: m0 is no product)
+    constexpr bool kSersic = MODEL == SHAPE_SERSIC;
+    const T px_x[7] = {h, h, h, h, kSersic ? (kFold ? m0 : px.c) : px.cR,
+                       kSersic ? px.c : m0 * px.q5, m0};
+    const T px_y[7] = {n1, n2, P2, P3, kFold ? px.t : t.k4, kSersic ? px.q5 : t.k5a, (T)1};
     const double rd = (double)r;
     if constexpr (kFlush > 0)
       c2p = first ? r * r : A::fma(r, r, c2p);
@@ -451,75 +692,52 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
         for (int c = a; c < 8; ++c) {
           if (!has(EM, c)) continue;
           if (c == 7 && a == 7) continue;   // the count of pixels, set by the caller
+          if (!in_sums(SUMS, a, c)) continue;
           if (c == 7)
-            acc.A[tri(a, c)] += J[a];
+            acc.A[tri(a, c)] = add_product<kFused>(px_x[a], px_y[a], J[a], acc.A[tri(a, c)]);
           else
             acc.A[tri(a, c)] = A::fma(J[a], J[c], acc.A[tri(a, c)]);
         }
       }
     }
   };
-  // The moment form's pixel (kMom): the Sersic render as in pixel(), then the
-  // H_j sums; the Re, n, I0 and sky columns are summed among themselves as
-  // there.  The FP32 instance takes R^2 in units of Re^2, s = R^2 S with
-  // S = 1 / Re^2 (2^(hc / ha)): then t = 2^(ha log2 s) needs no added
-  // constant, and t / R^2 = S 2^((ha - 1) log2 s) gives h without a
-  // reciprocal (one transcendental fewer per pixel; S goes into the folded
-  // factor of the x0, y0, e1, e2 columns, log2 S into the n column's
-  // constant).  The FP64 instance (the adjoint's; its exp2 costs more than
-  // its reciprocal) renders as pixel() does, with the factors k7 and k4 in
-  // the columns, and sums J^T J only when asked for.
+  // The moment form's pixel (kMom): the H_j sums; the Re, n, I0 and sky columns
+  // are summed among themselves as in pixel().
   constexpr bool kF32Mom = kMom && sizeof(T) == 4;
-  T mS = (T)1, mFloor = A::kR2Floor, mHam1 = (T)0, mK5b = (T)0;
-  if constexpr (kF32Mom) {
-    const T lS = A::uni(t.hc * A::rcp(t.ha));
-    mS = A::uni(A::ex2(lS));
-    mFloor = A::uni(A::kR2Floor * mS);
-    mHam1 = A::uni(t.ha - (T)1);
-    mK5b = A::uni(A::fma(-lS, t.k5a, t.k5b));
-  }
-  auto mom_pixel = [&](const T d, const T u2, T s2, const bool first) {
-    const bool floored = s2 < mFloor;
-    s2 = floored ? mFloor : s2;
-    const T L = A::lg2(s2);
-    T m0, c, h;
-    if constexpr (kF32Mom) {
-      const T tr = A::ex2(L * mHam1);   // t / s
-      const T tt = tr * s2;
-      m0 = A::ex2(t.nb2 * tt);
-      c = m0 * tt;
-      h = m0 * tr;                      // h / S
-    } else {
-      const T tt = A::ex2(A::fma(L, t.ha, t.hc));
-      m0 = A::ex2(t.nb2 * tt);
-      c = m0 * tt;
-      h = c * A::rcp(s2) * t.k7;
-    }
-    h = floored ? (T)0 : h;
+  const MomentUnits<T> mu = [&] {
+    if constexpr (kMom)
+      return MomentUnits<T>(t);
+    else
+      return MomentUnits<T>();
+  }();
+  auto mom_pixel = [&](auto fused, const float d, const T u2, const T s2, const bool first) {
+    constexpr bool kFused = decltype(fused)::value;
+    const Px<T> px = render_moment<DT, EM>(t, mu, d, st.scale, s2);
+    const T m0 = px.m0, c = px.c, h = px.h, r = px.r;
     T J[8];
     J[4] = kF32Mom ? c : c * t.k4;
-    if constexpr (has(EM, 5)) J[5] = c * A::fma(L, t.k5a, kF32Mom ? mK5b : t.k5b);
+    if constexpr (has(EM, 5)) J[5] = c * px.q5;
     J[6] = m0;
     J[7] = (T)1;
-    const T r = d - A::fma(t.I0, m0, t.sky);
-    T H[kMomN];
+    T H[3];
     H[0] = h;
 #pragma unroll
-    for (int j = 1; j < kMomN; ++j) H[j] = H[j - 1] * u2;
+    for (int j = 1; j < 3; ++j) H[j] = H[j - 1] * u2;
     if constexpr (kFlush > 0) {
       c2p = first ? r * r : A::fma(r, r, c2p);
 #pragma unroll
-      for (int j = 0; j < kMomN; ++j) gq[j] = first ? H[j] * r : A::fma(H[j], r, gq[j]);
+      for (int j = 0; j < 3; ++j) gq[j] = first ? H[j] * r : A::fma(H[j], r, gq[j]);
     } else {
       acc.c2 = fma((double)r, (double)r, acc.c2);
 #pragma unroll
-      for (int j = 0; j < kMomN; ++j) gm[j] = fma((double)H[j], (double)r, gm[j]);
+      for (int j = 0; j < 3; ++j) mom.g[j] = fma((double)H[j], (double)r, mom.g[j]);
     }
     if constexpr (JTJ) {
 #pragma unroll
-      for (int s = 0; s < 2 * kMomN - 1; ++s) {
-        const int i = s < kMomN ? s : kMomN - 1, j = s - i;   // H_i H_j, i + j = s
-        mM[s] = A::fma(H[i], H[j], mM[s]);
+      for (int s = 0; s < 5; ++s) {
+        if (!(SUMS & kSumsShape)) continue;
+        const int i = s < 3 ? s : 2, j = s - i;   // H_i H_j, i + j = s
+        mom.M[s] = A::fma(H[i], H[j], mom.M[s]);
       }
     }
 #pragma unroll
@@ -531,16 +749,23 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
         acc.g[a] = (a == 7) ? acc.g[a] + (double)r : fma((double)J[a], (double)r, acc.g[a]);
       if constexpr (JTJ) {
 #pragma unroll
-        for (int j = 0; j < kMomN; ++j)
-          if (a == 7)
-            mY[j] += H[j];
+        for (int j = 0; j < 3; ++j)
+          if (!(SUMS & (a == 7 ? kSumsProfile : kSumsCross)))
+            continue;
+          else if (a == 7)
+            mom.Y[j] = j == 0 ? mom.Y[0] + h
+                              : add_product<kFused>(H[j > 0 ? j - 1 : 0], u2, H[j], mom.Y[j]);
           else
-            mX[a - 4][j] = A::fma(H[j], J[a], mX[a - 4][j]);
+            mom.X[a - 4][j] = A::fma(H[j], J[a], mom.X[a - 4][j]);
 #pragma unroll
         for (int c2 = a; c2 < 8; ++c2) {
-          if (!has(EM, c2) || (c2 == 7 && a == 7)) continue;
+          if (!has(EM, c2) || (c2 == 7 && a == 7) || !in_sums(SUMS, a, c2)) continue;
           if (c2 == 7)
-            acc.A[tri(a, c2)] += J[a];
+            acc.A[tri(a, c2)] =
+                a == 4   ? add_product<kFused>(kF32Mom ? m0 : c, kF32Mom ? px.t : t.k4, J[4],
+                                               acc.A[tri(a, c2)])
+                : a == 5 ? add_product<kFused>(c, px.q5, J[5], acc.A[tri(a, c2)])
+                         : acc.A[tri(a, c2)] + m0;
           else
             acc.A[tri(a, c2)] = A::fma(J[a], J[c2], acc.A[tri(a, c2)]);
         }
@@ -552,12 +777,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     const int lane = tid < 0 ? (int)(threadIdx.x & (kWave - 1)) : tid;
     const int sd = st.side;                      // 8, 16, 32 or 64
     // the lane's column: u1 fixed, the quadratics' per-column coefficients
-    const T u1 = (T)(lane & (sd - 1)) - t.x0;
-    const T uu = u1 * u1;
-    const T qb = t.qb1 * u1, qc = t.qc2 * uu;
-    const T p2b = t.e1 * qb, p2c = A::fma(t.e1, qc, -t.a11 * uu);
-    const T p3b = A::fma(t.e2, qb, (T)-2 * u1), p3c = A::fma(t.e2, qc, -t.a12 * uu);
-    const T c3 = t.n11 * u1, c4 = t.n12 * u1;
+    const Column<T> col(t, (T)(lane & (sd - 1)) - t.x0);
     const T di = (T)(kWave / sd);
     T u2 = (T)(lane / sd) - t.y0;
     const int nstep = st.npix / kWave;
@@ -574,24 +794,27 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     // unrolled run too few registers (136 spilled, 4x slower).
     constexpr int kRun = 8;
     static_assert(kFlush == 0 || kFlush == kRun, "a run is one partial-sum block");
-    constexpr bool kUnroll = DT == SHAPE_F32 && (sizeof(T) == 4 || EM == 0u || JTJ);
+    // The sweeps of part of the sums (SUMS), one wave per SIMD with registers to
+    // spare, are unrolled in either storage.
+    constexpr bool kPart = SUMS != kSumsAll;
+    constexpr bool kUnroll = kPart || (DT == SHAPE_F32 && (sizeof(T) == 4 || EM == 0u || JTJ));
+    using RunFused = std::bool_constant<kMom || DT == SHAPE_F32>;   // sums_fused of whole runs
     const bool blocked = kUnroll && nstep % kRun == 0;   // wave-uniform
     // R^2 S along the column (the moment form's units)
-    const T qas = A::uni(t.qa * mS), qbs = qb * mS, qcs = qc * mS;
-    auto row_pixel = [&](const T d, const T u2, const bool first) {
+    const T qas = A::uni(t.qa * mu.S), qbs = col.qb * mu.S, qcs = col.qc * mu.S;
+    auto row_pixel = [&](auto fused, const float d, const T u2, const bool first) {
       if constexpr (kMom)
-        mom_pixel(d, u2, A::fma(A::fma(qas, u2, qbs), u2, qcs), first);
+        mom_pixel(fused, d, u2, A::fma(A::fma(qas, u2, qbs), u2, qcs), first);
       else
-        pixel(d, A::fma(A::fma(t.qa, u2, qb), u2, qc), A::fma(t.n12, u2, c3),
-              A::fma(t.n22, u2, c4), A::fma(A::fma(t.p2a, u2, p2b), u2, p2c),
-              A::fma(A::fma(t.p3a, u2, p3b), u2, p3c), first);
+        pixel(fused, d, col.R2(t, u2), col.n1(t, u2), col.n2(t, u2), col.P2(t, u2), col.P3(t, u2),
+              first);
     };
     if (blocked) {
 #pragma unroll 1
       for (int m0 = 0; m0 < nstep; m0 += kRun) {
 #pragma unroll
         for (int q = 0; q < kRun; ++q) {
-          row_pixel((T)load_rel<DT>(sp, k + (uint32_t)(q * kWave), st.scale), u2, q == 0);
+          row_pixel(RunFused(), load_raw<DT>(sp, k + (uint32_t)(q * kWave)), u2, q == 0);
           u2 += di;
         }
         k += (uint32_t)(kRun * kWave);
@@ -605,12 +828,12 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     if (peeled) {
 #pragma unroll 1
       for (int m0 = 0; m0 < nstep; m0 += kRun) {
-        row_pixel((T)load_rel<DT>(sp, k, st.scale), u2, true);
+        row_pixel(std::true_type(), load_raw<DT>(sp, k), u2, true);
         u2 += di;
         k += kWave;
 #pragma unroll 1
         for (int q = 1; q < kRun; ++q) {
-          row_pixel((T)load_rel<DT>(sp, k, st.scale), u2, false);
+          row_pixel(std::true_type(), load_raw<DT>(sp, k), u2, false);
           u2 += di;
           k += kWave;
         }
@@ -620,7 +843,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     if (!blocked && !peeled) {
 #pragma unroll 1
       for (int m = 0; m < nstep; ++m) {
-        row_pixel((T)load_rel<DT>(sp, k, st.scale), u2, false);
+        row_pixel(std::false_type(), load_raw<DT>(sp, k), u2, false);
         u2 += di;
         k += kWave;
         if constexpr (kFlush > 0)
@@ -628,84 +851,18 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
       }
     }
     if constexpr (kMom) {
-      // the column sums from the moments, per lane, in FP64: column k is
-      // h sum_j C[k][j] u2^j (degree 1 for x0, y0, 2 for e1, e2)
       flush();
-      // the FP32 instance folds the factor k7 S of these columns (and k4 of
-      // the Re column) in here, not into the sums afterwards
-      const double f7 = kF32Mom ? (double)(t.k7 * mS) : 1.0;
-      const double f4 = kF32Mom ? (double)t.k4 : 1.0;
-      const double C[4][3] = {{c3 * f7, t.n12 * f7, 0.0},
-                              {c4 * f7, t.n22 * f7, 0.0},
-                              {p2c * f7, p2b * f7, t.p2a * f7},
-                              {p3c * f7, p3b * f7, t.p3a * f7}};
-      double M[5], X[3][3], Y[3];
-#pragma unroll
-      for (int s = 0; s < 5; ++s) M[s] = (double)mM[s];
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        Y[j] = (double)mY[j];
-#pragma unroll
-        for (int v = 0; v < 3; ++v) X[v][j] = (double)mX[v][j] * (v == 0 ? f4 : 1.0);
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        const int da = a < 2 ? 2 : 3;   // coefficients of column a
-        double g = 0.0, y = 0.0, x[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-        for (int j = 0; j < da; ++j) {
-          g = fma(C[a][j], gm[j], g);
-          y = fma(C[a][j], Y[j], y);
-#pragma unroll
-          for (int v = 0; v < 3; ++v) x[v] = fma(C[a][j], X[v][j], x[v]);
-        }
-        acc.g[a] = g;
-        if constexpr (JTJ) {
-          if (has(EM, 7)) acc.A[tri(a, 7)] = (T)y;
-#pragma unroll
-          for (int v = 0; v < 3; ++v)
-            if (has(EM, 4 + v)) acc.A[tri(a, 4 + v)] = (T)x[v];
-        }
-      }
-      // P[c][i] = sum_j C[c][j] M[i + j]; entry (a, c) = sum_i C[a][i] P[c][i]
-      if constexpr (JTJ) {
-        double P[4][3];
-#pragma unroll
-        for (int c2 = 0; c2 < 4; ++c2) {
-          const int dc = c2 < 2 ? 2 : 3;
-#pragma unroll
-          for (int i = 0; i < 3; ++i) {
-            double q = 0.0;
-#pragma unroll
-            for (int j = 0; j < dc; ++j) q = fma(C[c2][j], M[i + j], q);
-            P[c2][i] = q;
-          }
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          const int da = a < 2 ? 2 : 3;
-#pragma unroll
-          for (int c2 = a; c2 < 4; ++c2) {
-            double q = 0.0;
-#pragma unroll
-            for (int i = 0; i < da; ++i) q = fma(C[a][i], P[c2][i], q);
-            acc.A[tri(a, c2)] = (T)q;
-          }
-        }
-      }
+      recombine<EM, JTJ, kGrad, (SUMS & kSumsProfile) != 0u, (SUMS & kSumsCross) != 0u,
+                (SUMS & kSumsShape) != 0u>(t, mu, col, mom, acc);
     }
   } else {
     // the lane-stride walk (any side, any team), directly or through LDS
     auto any_walk = [&]() {
       int cnt = 0;
       // pixel (i, j) with value d, in the lane-stride order of for_pixels
-      auto any_pixel = [&](const T d, int i, int j) {
-        const T u1 = (T)j - t.x0, u2 = (T)i - t.y0;
-        // (v1, v2) = S(e) u
-        const T v1 = A::fma(t.a11, u1, t.a12 * u2), v2 = A::fma(t.a12, u1, t.a22 * u2);
-        const T R2 = A::fma(v1, v1, v2 * v2) * t.invD;
-        pixel(d, R2, A::fma(t.n11, u1, t.n12 * u2), A::fma(t.n12, u1, t.n22 * u2),
-              A::fma(t.e1, R2, A::fma(v2, u2, -v1 * u1)), A::fma(t.e2, R2, -A::fma(v1, u2, v2 * u1)));
+      auto any_pixel = [&](const float d, int i, int j) {
+        const Walk<T> wk(t, (T)j - t.x0, (T)i - t.y0);
+        pixel(std::false_type(), d, wk.R2, wk.n1, wk.n2, wk.P2, wk.P3);
         if constexpr (kFlush > 0) {
           if (++cnt == kFlush) {
             flush();
@@ -741,8 +898,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
 #pragma unroll 1
           for (; k < k0 + nb; k += STRIDE) {
             const E e = buf[k - k0];
-            const T d = DT == SHAPE_F32 ? (T)(float)e : (T)((float)e * st.scale);
-            any_pixel(d, i, j);
+            any_pixel((float)e, i, j);
             i += di;
             j += dj;
             if (j >= side) {
@@ -752,8 +908,42 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
           }
         }
       } else {
+        const void* sp = stamp_base<DT>(b, st);
+        if constexpr (SUMS != kSumsAll) {
+          // part of the sums: in unrolled runs, whose loads issue together
+          // (rolled, each pixel waits for its load: one wave per SIMD)
+          static_assert(STRIDE == kWave && kFlush == 8, "one wave, runs of one partial");
+          const int side = st.side, npix = st.npix;
+          const int t0 = tid < 0 ? (int)(threadIdx.x & (kWave - 1)) : tid;
+          int i = t0 / side, j = t0 - i * side;
+          const int di = kWave / side, dj = kWave - di * side;
+#pragma unroll 1
+          for (int k0 = 0; k0 < npix; k0 += kFlush * kWave) {
+            float d[kFlush];
+#pragma unroll
+            for (int q = 0; q < kFlush; ++q) {
+              const int k = k0 + q * kWave + t0;
+              d[q] = load_raw<DT>(sp, (uint32_t)(k < npix ? k : npix - 1));
+            }
+#pragma unroll
+            for (int q = 0; q < kFlush; ++q) {
+              if (k0 + q * kWave + t0 < npix) {
+                const Walk<T> wk(t, (T)j - t.x0, (T)i - t.y0);
+                pixel(std::false_type(), d[q], wk.R2, wk.n1, wk.n2, wk.P2, wk.P3);
+              }
+              i += di;
+              j += dj;
+              if (j >= side) {
+                j -= side;
+                ++i;
+              }
+            }
+            flush();
+          }
+          return;
+        }
         for_pixels<STRIDE>(st.side, [&](int k, int i, int j) {
-          any_pixel((T)load_px<DT>(b.pixels, st.off, k, st.scale), i, j);
+          any_pixel(load_raw<DT>(sp, (uint32_t)k), i, j);
         }, tid);
       }
   
@@ -770,27 +960,21 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
           const int sg = s0 + lane;
           const bool on = sg < S;
           const int g = on ? sg / W : 0, j = on ? sg - g * W : 0, r0 = g * kSegRows;
-          const T u1 = (T)j - t.x0;
-          const T uu = u1 * u1;
-          const T qb = t.qb1 * u1, qc = t.qc2 * uu;
-          const T p2b = t.e1 * qb, p2c = A::fma(t.e1, qc, -t.a11 * uu);
-          const T p3b = A::fma(t.e2, qb, (T)-2 * u1), p3c = A::fma(t.e2, qc, -t.a12 * uu);
-          const T c3 = t.n11 * u1, c4 = t.n12 * u1;
+          const Column<T> col(t, (T)j - t.x0);
           // the segment's pixels (rows past the stamp read its last row and are
           // skipped below), loaded back to back
-          T d[kSegRows];
+          float d[kSegRows];
 #pragma unroll
           for (int q = 0; q < kSegRows; ++q) {
             const int i = r0 + q < last ? r0 + q : last;
-            d[q] = (T)load_rel<DT>(sp, (uint32_t)(i * W + j), st.scale);
+            d[q] = load_raw<DT>(sp, (uint32_t)(i * W + j));
           }
 #pragma unroll
           for (int q = 0; q < kSegRows; ++q) {
             if (on && r0 + q < W) {
               const T u2 = (T)(r0 + q) - t.y0;
-              pixel(d[q], A::fma(A::fma(t.qa, u2, qb), u2, qc), A::fma(t.n12, u2, c3),
-                    A::fma(t.n22, u2, c4), A::fma(A::fma(t.p2a, u2, p2b), u2, p2c),
-                    A::fma(A::fma(t.p3a, u2, p3b), u2, p3c));
+              pixel(std::true_type(), d[q], col.R2(t, u2), col.n1(t, u2), col.n2(t, u2),
+                    col.P2(t, u2), col.P3(t, u2));
             }
           }
           flush();   // one partial per segment

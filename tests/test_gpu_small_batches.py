@@ -48,3 +48,76 @@ def test_mixed_sides_one_launch_equals_launch_per_form(shape, storage):
     assert got[0][2][11] == shape.ST_NONFINITE_INPUT
     for a, c in zip(*got):
         np.testing.assert_array_equal(a, c)
+
+
+def _one_side(shape, side, storage, model):
+    """24 stamps of one side cut around the galaxies (or stars) of larger ones,
+    tiled to a batch beyond the split fit's limit."""
+    import torch
+    src = synth.make("stars32" if model else "sersic64", count=24)
+    w = int(src.sides[0])
+    rng = np.random.default_rng(side)
+    img = src.pixels.reshape(24, w, w).astype(np.float32)
+    pix = 10.0 + rng.normal(0, 1.0, (24, side, side)).astype(np.float32) * src.sigma[:24, None, None]
+    a, c = max(0, (w - side) // 2), max(0, (side - w) // 2)
+    m = min(w, side)
+    pix[:, c:c + m, c:c + m] = img[:, a:a + m, a:a + m]
+    scale = None
+    if storage == "f16":
+        scale = np.exp2(np.ceil(np.log2(np.abs(pix).reshape(24, -1).max(1) / 32768.0)))
+        scale = scale.astype(np.float32)
+        pix = (pix / scale[:, None, None]).astype(np.float16)
+    out = []
+    for k in (1, SPLIT_LIMIT // 24 + 1):
+        t = lambda x: torch.from_numpy(np.tile(x, (k,) + (1,) * (x.ndim - 1))).cuda()   # noqa: E731
+        out.append(shape.DeviceBatch(
+            pixels=t(pix).reshape(-1), sigma=t(src.sigma[:24].astype(np.float32)), side0=side,
+            scale=None if scale is None else t(scale),
+            model=t(np.full(24, model, np.uint8)) if model else None))
+    return out
+
+
+SPLIT_LIMIT = 8192   # (the library's limits are not above this)
+
+
+def _same_fits(shape, small, large, opts):
+    import torch
+    got = []
+    for batch in (small, large):
+        rec0, _, _ = shape.centroid(batch)
+        rec, _, _ = shape.moments(batch, rec0)
+        f = shape.fit_sersic(batch, rec=rec, opts=opts, want_perr=True)
+        torch.cuda.synchronize()
+        got.append({k: v[:small.n].cpu().numpy() for k, v in f.items()})
+    for k in got[0]:
+        np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
+    return got[0]
+
+
+# Every layout of a sweep at the ends of its range: sides 8 to 64 that divide
+# 64 (columns; 1, 4, 16 and 64 steps), other sides up to 64 (the walk; one
+# step, a ragged last one, several chunks), sides above (segments).
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("side,model", [(8, 0), (16, 0), (32, 0), (64, 0), (4, 0), (7, 0), (33, 0),
+                                        (48, 0), (63, 0), (65, 0), (96, 0), (128, 0), (32, 1),
+                                        (47, 1), (81, 1)])
+def test_split_fit_equals_one_wave_fit(shape, side, model, storage):
+    """Four waves per stamp against one wave per stamp (a larger batch)."""
+    small, large = _one_side(shape, side, storage, model)
+    for kw in (dict(), dict(free_mask=shape.MASK_SIZE),
+               dict(free_mask=shape.MASK_SIZE, linear_init=0), dict(max_iter_lm=1)):
+        if model and "linear_init" in kw:
+            continue
+        r = _same_fits(shape, small, large, shape.default_opts(**kw))
+        if side >= 32 and not kw:
+            assert ((r["status"] & shape.ST_CONVERGED) != 0).sum() >= 12
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_split_fit_of_mixed_sides_and_models(shape, storage):
+    b = synth.make("uneven", count=512, storage=storage)
+    db = shape.DeviceBatch.from_host(b, "cuda:0", uniform=False)
+    db.sides[8] = 3
+    db.sigma[10] = -1.0
+    db.pixels[int(b.offsets[11])] = float("nan")
+    _same_fits(shape, db, _repeat(shape, db, SPLIT_LIMIT + 1), shape.default_opts())
