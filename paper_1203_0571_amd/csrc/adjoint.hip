@@ -3,103 +3,173 @@
 //
 // With r_i = (d_i - m_i) / sigma the adjoint of pixel i is
 //   dL/dm_i = -(2 / sigma) r_i dL/dchi2,
-// and dL/dp_k = sum_i dL/dm_i dm_i/dp_k.  The backward sweep is the device
-// function the fit uses for its J^T r and J^T J, instantiated in FP64 (FP64
-// render, Jacobian and sums; log2 / exp2 by 64-point tables and short
-// series): the FP32 instance's rounding of the exponent b t is amplified
-// where the gradient components cancel over the stamp, up to ~1e-4 of the
-// largest component.  J^T J is summed only when it is asked for.
+// and dL/dp_k = sum_i dL/dm_i dm_i/dp_k.  Render, Jacobian and sums are FP64
+// (adjoint_sweep.hpp for Sersic stamps, sweep.hpp's FP64 instance for Moffat
+// stamps, each a kernel of its own so that neither holds the other's
+// registers): the FP32 rounding of the exponent b t is amplified where the
+// gradient components cancel over the stamp, up to ~1e-4 of the largest
+// component.  J^T J is summed only when it is asked for.
 #include "kernels.hpp"
-#include "sweep.hpp"
+#include "adjoint_sweep.hpp"
 
 namespace shape {
 namespace {
 
-// GRAD: also J^T r (the gradient); JTJ: also J^T J (the normal matrix).
-template <int DT, int MODEL, bool GRAD, bool JTJ>
-__global__ __launch_bounds__(kWave, JTJ ? 2 : 5) void chi2_kernel(shape_batch b, const float* params,
-                                                     const float* grad_chi2, float* chi2,
-                                                     float* grad_p, float* jtj, float* jtr) {
+// What the caller gets for a stamp that cannot be evaluated, by one thread.
+template <bool GRAD>
+__device__ __forceinline__ void write_nan(int64_t s, float* chi2, float* grad_p, float* jtj,
+                                          float* jtr) {
+  if (chi2) chi2[s] = qnan();
+  if constexpr (GRAD) {
+    for (int k = 0; k < 8; ++k) {
+      grad_p[s * 8 + k] = qnan();
+      if (jtr) jtr[s * 8 + k] = qnan();
+    }
+    if (jtj)
+      for (int k = 0; k < 36; ++k) jtj[s * 36 + k] = qnan();
+  }
+}
+
+// A stamp's parameters; false when one is not finite.
+__device__ __forceinline__ bool read_params(const float* params, int64_t s, double (&p)[8]) {
+  bool finite = true;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    p[k] = params[s * 8 + k];
+    finite = finite && __builtin_isfinite(p[k]);
+  }
+  return finite;
+}
+
+// Reduce a wave's sums and write the stamp's outputs.
+template <bool GRAD, bool JTJ>
+__device__ __forceinline__ void write_sums(const Acc<GRAD ? 0xFFu : 0u, double>& acc,
+                                           const Stamp& st, int64_t s, const float* grad_chi2,
+                                           float* chi2, float* grad_p, float* jtj, float* jtr,
+                                           int lane) {
+  // chi^2 and J^T r: one pass of FP64 wave sums over 12 values (every lane
+  // receives the totals)
+  double u[12];
+  u[0] = acc.c2;
+  if constexpr (GRAD) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) u[1 + k] = acc.g[k];
+    u[9] = u[10] = u[11] = 0.0;
+    wave_sum_n(u);
+  } else {
+    // chi^2 alone, by the same tree of additions
+    double v[4] = {acc.c2, 0.0, 0.0, 0.0};
+    wave_sum_n(v);
+    u[0] = v[0];
+  }
+  const double inv2 = 1.0 / (st.sigma * st.sigma);
+  if (lane == 0) {
+    if (chi2) chi2[s] = (float)(u[0] * inv2);
+    if constexpr (GRAD) {
+      const double up = grad_chi2 ? (double)grad_chi2[s] : 1.0;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        grad_p[s * 8 + k] = (float)(-2.0 * up * u[1 + k] * inv2);
+        if (jtr) jtr[s * 8 + k] = (float)(u[1 + k] * inv2);
+      }
+    }
+  }
+  if constexpr (JTJ) {
+    double v[36];
+#pragma unroll
+    for (int k = 0; k < 36; ++k) v[k] = acc.A[k];
+    wave_sum_n(v);
+    if (lane == 0) {
+#pragma unroll
+      for (int k = 0; k < 36; ++k)
+        jtj[s * 36 + k] = (k == tri(7, 7)) ? (float)(st.npix * inv2) : (float)(v[k] * inv2);
+    }
+  }
+}
+
+// The Sersic stamps of a batch, `chunk` to a workgroup of one wave.  GRAD: also
+// J^T r (the gradient); JTJ: also J^T J (the normal matrix).  Waves per SIMD:
+// with the gradient 3 (64 x 64 FP32 660 us; 4 spill more per stamp: 695, and 16 x
+// 16 314 -> 379; 2: 744), with J^T J 2, for chi^2 alone 5.
+template <int DT, bool GRAD, bool JTJ>
+__global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_sersic_kernel(
+    shape_batch b, const float* params, const float* grad_chi2, float* chi2, float* grad_p,
+    float* jtj, float* jtr, int chunk) {
+  __shared__ SersicTables tab;
+  const int lane = threadIdx.x;
+  sersic_tables_fill(tab, lane);
+  for (int64_t s0 = (int64_t)blockIdx.x * chunk; s0 < b.n; s0 += (int64_t)gridDim.x * chunk) {
+    const int n = (int)(b.n - s0 < chunk ? b.n - s0 : chunk);
+    wave_sync();   // the previous chunk's constants have been read
+    if (lane < n) {
+      const int64_t s = s0 + lane;
+      const Stamp st = stamp_info(b, s);
+      int todo = kSkip;   // the other model's launch owns it
+      if (st.bad || st.model == SHAPE_SERSIC) {
+        double p[8];
+        if (!read_params(params, s, p) || st.bad) {
+          write_nan<GRAD>(s, chi2, grad_p, jtj, jtr);
+        } else {
+          tab.t[lane] = make_trial<double, false>(p, SHAPE_SERSIC, 0.0);
+          todo = sersic_covered(p, st.side) ? kCovered : kSeries;
+        }
+      }
+      tab.todo[lane] = todo;
+    }
+    wave_sync();
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+      const int todo = __builtin_amdgcn_readfirstlane(tab.todo[i]);
+      if (todo == kSkip) continue;
+      const Stamp st = stamp_info(b, s0 + i);
+      Acc<GRAD ? 0xFFu : 0u, double> acc;
+      if (todo == kCovered)
+        sersic_sweep<DT, GRAD, JTJ, true>(b, st, tab, tab.t[i], lane, acc);
+      else
+        sersic_sweep<DT, GRAD, JTJ, false>(b, st, tab, tab.t[i], lane, acc);
+      write_sums<GRAD, JTJ>(acc, st, s0 + i, grad_chi2, chi2, grad_p, jtj, jtr, lane);
+    }
+  }
+}
+
+// The Moffat stamps of a batch, one wave per stamp (sweep.hpp in FP64).
+template <int DT, bool GRAD, bool JTJ>
+__global__ __launch_bounds__(kWave, JTJ ? 2 : 5) void chi2_moffat_kernel(
+    shape_batch b, const float* params, const float* grad_chi2, float* chi2, float* grad_p,
+    float* jtj, float* jtr) {
   constexpr uint32_t EM = GRAD ? 0xFFu : 0u;
   const int lane = threadIdx.x;
   f64_tables_fill(lane, kWave);   // the FP64 log2 / exp2 tables
   wave_sync();
   for (int64_t s = blockIdx.x; s < b.n; s += gridDim.x) {
     const Stamp st = stamp_info(b, s);
-    if (!st.bad && st.model != MODEL) continue;  // the other model's launch owns it
-    if (st.bad && MODEL != SHAPE_SERSIC) continue;
+    if (st.bad || st.model != SHAPE_MOFFAT) continue;  // the Sersic launch's
     double p[8];
-    bool finite = true;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      p[k] = params[s * 8 + k];
-      finite = finite && __builtin_isfinite(p[k]);
-    }
-    if (st.bad || !finite) {
-      if (lane == 0) {
-        if (chi2) chi2[s] = qnan();
-        if (GRAD) {
-          for (int k = 0; k < 8; ++k) {
-            grad_p[s * 8 + k] = qnan();
-            if (jtr) jtr[s * 8 + k] = qnan();
-          }
-          if (jtj)
-            for (int k = 0; k < 36; ++k) jtj[s * 36 + k] = qnan();
-        }
-      }
+    if (!read_params(params, s, p)) {
+      if (lane == 0) write_nan<GRAD>(s, chi2, grad_p, jtj, jtr);
       continue;
     }
     Acc<EM, double> acc;
-    // a side that divides 64 takes the column-per-lane layout (the geometry
-    // as per-column quadratics), any other side the lane-stride walk
-    const Trial<double> tr = make_trial<double>(p, MODEL, p[5]);
-    if (rows_layout_fits(st.side))
-      sweep<DT, MODEL, EM, kWave, double, kLayoutRows, JTJ>(b, st, tr, acc);
-    else
-      sweep<DT, MODEL, EM, kWave, double, kLayoutAny, JTJ>(b, st, tr, acc);
-    // chi^2 and J^T r: one pass of FP64 wave sums over 12 values (every lane
-    // receives the totals)
-    double u[12];
-    u[0] = acc.c2;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) u[1 + k] = GRAD ? acc.g[k] : 0.0;
-    u[9] = u[10] = u[11] = 0.0;
-    wave_sum_n(u);
-    const double inv2 = 1.0 / (st.sigma * st.sigma);
-    if (lane == 0) {
-      if (chi2) chi2[s] = (float)(u[0] * inv2);
-      if constexpr (GRAD) {
-        const double up = grad_chi2 ? (double)grad_chi2[s] : 1.0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          grad_p[s * 8 + k] = (float)(-2.0 * up * u[1 + k] * inv2);
-          if (jtr) jtr[s * 8 + k] = (float)(u[1 + k] * inv2);
-        }
-      }
-    }
-    if constexpr (JTJ) {
-      double v[36];
-#pragma unroll
-      for (int k = 0; k < 36; ++k) v[k] = acc.A[k];
-      wave_sum_n(v);
-      if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 36; ++k)
-          jtj[s * 36 + k] = (k == tri(7, 7)) ? (float)(st.npix * inv2) : (float)(v[k] * inv2);
-      }
-    }
+    sweep<DT, SHAPE_MOFFAT, EM, kWave, double, kLayoutAny, JTJ>(
+        b, st, make_trial<double>(p, SHAPE_MOFFAT, p[5]), acc);
+    write_sums<GRAD, JTJ>(acc, st, s, grad_chi2, chi2, grad_p, jtj, jtr, lane);
   }
 }
 
 template <int DT, bool GRAD, bool JTJ>
 hipError_t launch_dt(const shape_batch& b, const float* params, const float* grad_chi2,
                      float* chi2, float* grad_p, float* jtj, float* jtr, hipStream_t stream) {
-  const int64_t grid = b.n < (1ll << 30) ? b.n : (1ll << 30);
-  hipLaunchKernelGGL((chi2_kernel<DT, SHAPE_SERSIC, GRAD, JTJ>), dim3((unsigned)grid),
-                     dim3(kWave), 0, stream, b, params, grad_chi2, chi2, grad_p, jtj, jtr);
+  // chunks of up to kChi2Chunk stamps that still make 8,192 workgroups, a few
+  // rounds over the card
+  const int64_t most = b.n / 8192, chunk = most < 1 ? 1 : most > kChi2Chunk ? kChi2Chunk : most;
+  const int64_t groups = (b.n + chunk - 1) / chunk, cap = 1ll << 25;
+  hipLaunchKernelGGL((chi2_sersic_kernel<DT, GRAD, JTJ>),
+                     dim3((unsigned)(groups < cap ? groups : cap)), dim3(kWave), 0, stream, b,
+                     params, grad_chi2, chi2, grad_p, jtj, jtr, (int)chunk);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !b.model) return e;
-  hipLaunchKernelGGL((chi2_kernel<DT, SHAPE_MOFFAT, GRAD, JTJ>), dim3((unsigned)grid),
+  const int64_t grid = b.n < (1ll << 30) ? b.n : (1ll << 30);
+  hipLaunchKernelGGL((chi2_moffat_kernel<DT, GRAD, JTJ>), dim3((unsigned)grid),
                      dim3(kWave), 0, stream, b, params, grad_chi2, chi2, grad_p, jtj, jtr);
   return hipGetLastError();
 }

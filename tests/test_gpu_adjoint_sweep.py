@@ -1,0 +1,95 @@
+"""GPU: the FP64 sweep behind chi2_fwd / chi2_bwd over its pixel layouts (how a
+side is cut into runs of rows) and its two series (tabulated powers; the full
+series for stamps the tables do not cover), against the FP64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_adjoint import _check_grad
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def shape():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_1203_0571_amd as shape
+    return shape
+
+
+def _stamps(side, storage, n=16):
+    """Stamps of noise and parameters; from stamp 10 on ones the tables miss."""
+    rng = np.random.default_rng(side)
+    c = 0.5 * (side - 1)
+    p = np.empty((n, 8))
+    p[:, 0:2] = c + rng.uniform(-0.9, 0.9, (n, 2))
+    r, th = rng.uniform(0, 0.7, n), rng.uniform(0, 2 * np.pi, n)
+    p[:, 2], p[:, 3] = r * np.cos(th), r * np.sin(th)
+    p[:, 4] = rng.uniform(0.08, 0.3, n) * side
+    p[:, 5] = rng.uniform(0.4, 6.0, n)
+    p[:, 6] = rng.uniform(1.0, 100.0, n)
+    p[:, 7] = rng.uniform(-5.0, 5.0, n)
+    p[0, 0] = -2.25                 # the centre outside the stamp
+    p[10, 0:2] = np.floor(c)        # on a pixel: the model's floor
+    p[11, 2:4] = 0.9995, 0.0        # |e| beyond the tables' range
+    p[12, 4] = 2e5                  # Re beyond it
+    p[13, 0:2] = np.floor(c) + [1e-4, 0.0]   # R^2 below it
+    p[14, 2] = np.nan
+    p = p.astype(np.float32).astype(np.float64)
+    pix = rng.normal(3.0, 2.0, (n, side, side)).astype(np.float32)
+    if storage == "f16":
+        pix = pix.astype(np.float16)
+    return p, pix, rng.uniform(1.0, 3.0, n).astype(np.float32)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("side", [4, 5, 8, 16, 31, 33, 48, 63, 64, 65, 100, 128])
+def test_sersic_sweep_vs_oracle(shape, side, storage):
+    """Outputs are FP64 sums (series good to 5e-14) rounded to FP32 (6e-8): 1e-6
+    of each, and of entries down to 1e-3 of the largest where terms cancel."""
+    import torch
+    p, pix, sigma = _stamps(side, storage)
+    n = len(p)
+    scale = torch.full((n,), 0.5, device="cuda") if storage == "f16" else None
+    db = shape.DeviceBatch(pixels=torch.from_numpy(pix).cuda().reshape(-1),
+                           sigma=torch.from_numpy(sigma).cuda(), side0=side, scale=scale)
+    pt = torch.from_numpy(p.astype(np.float32)).cuda()
+    value = shape.chi2_fwd(db, pt).cpu().numpy()
+    plain = {k: v.cpu().numpy() for k, v in shape.chi2_bwd(db, pt).items() if v is not None}
+    full = {k: v.cpu().numpy() for k, v in shape.chi2_bwd(db, pt, want_normal=True).items()}
+    img = pix.astype(np.float64) * (0.5 if storage == "f16" else 1.0)
+    for out in (value, plain["chi2"], plain["grad"], full["grad"], full["jtj"]):
+        assert np.isnan(out[14]).all()
+    np.testing.assert_array_equal(plain["chi2"], value)
+    np.testing.assert_array_equal(full["chi2"], value)
+    for s in range(n):
+        if s == 14:
+            continue
+        c2, g, jtj = oracle.chi2(img[s], float(sigma[s]), p[s], want_grad=True)
+        assert abs(value[s] / c2 - 1) < 1e-6, s
+        for got in (plain, full):
+            err = _check_grad(got["grad"][s:s + 1].astype(np.float64), g[None], p[s:s + 1], sigma[s:s + 1])
+            assert err < 1e-6, (s, err)
+        # entry (k, l) in units of its columns' norms, the diagonal
+        d = np.sqrt([jtj[k * 8 - k * (k - 1) // 2] for k in range(8)])
+        unit = np.array([d[k] * d[m] for k in range(8) for m in range(k, 8)])
+        assert (np.abs(full["jtj"][s] - jtj) <= 1e-6 * np.maximum(np.abs(jtj), 1e-3 * unit)).all(), s
+
+
+def test_chunks_of_stamps_do_not_change_the_results(shape):
+    """A workgroup takes up to 8 stamps of a large batch and one of a small one."""
+    import torch
+    p, pix, sigma = _stamps(5, "f32")
+    model = np.zeros(len(p), np.uint8)
+    model[3::4] = 1
+    p[3::4, 5] = 3.0
+    out = []
+    for k in (1, 4097):     # 16 and 65,552 stamps
+        t = lambda x: torch.from_numpy(np.tile(x, (k,) + (1,) * (x.ndim - 1))).cuda()   # noqa: E731
+        db = shape.DeviceBatch(pixels=t(pix).reshape(-1), sigma=t(sigma), side0=5, model=t(model))
+        out.append(shape.chi2_bwd(db, t(p.astype(np.float32)), want_normal=True))
+    for key in ("chi2", "grad", "jtj"):
+        small, large = (o[key].cpu().numpy() for o in out)
+        np.testing.assert_array_equal(large.reshape((4097,) + small.shape),
+                                      np.broadcast_to(small, (4097,) + small.shape))
