@@ -69,6 +69,15 @@ __global__ __launch_bounds__(kWave, SHAPE_FIT_WAVES_PER_SIMD) void fit_kernel(
       sl.off = 0;
       fit_one<DT, MODEL, MASK, LAYOUT, PROF>(bl, o, sl, p_init, rec, s, W, p_out, chi2, perr,
                                              iters, status, sweeps, tid);
+    } else if constexpr (LAYOUT == kLayoutSegs) {
+      // each of the two forms with an LM loop of its own: in one loop that held
+      // both sweeps, each spilled for the other
+      if (st.side >= kSegsMinSide)
+        fit_one<DT, MODEL, MASK, kLayoutSegsOnly, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
+                                                        perr, iters, status, sweeps, tid);
+      else
+        fit_one<DT, MODEL, MASK, kLayoutAny, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
+                                                   iters, status, sweeps, tid);
     } else {
       fit_one<DT, MODEL, MASK, LAYOUT, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
                                              iters, status, sweeps, tid);

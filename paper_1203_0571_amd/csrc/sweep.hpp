@@ -306,12 +306,13 @@ __device__ __forceinline__ T residual(float raw, float scale, T m) {
 
 // Renders a pixel stored as `raw` at R^2 = R2 (unfloored).  The Sersic columns'
 // constant factors k7 (of x0, y0, e1, e2) and k4 (of Re) are left out: they are
-// applied to the sums once, after the sweep.
-template <int DT, int MODEL, uint32_t EM, typename T>
+// applied to the sums once, after the sweep.  FLOOR = false: the caller knows
+// that R2 is not below the model's floor (clear_of_floor).
+template <int DT, int MODEL, uint32_t EM, bool FLOOR, typename T>
 __device__ __forceinline__ Px<T> render(const Trial<T>& t, float raw, float scale, T R2) {
   using A = Arith<T>;
   Px<T> p;
-  const bool floored = R2 < A::kR2Floor;
+  const bool floored = FLOOR && R2 < A::kR2Floor;
   R2 = floored ? A::kR2Floor : R2;
   if constexpr (MODEL == SHAPE_SERSIC) {
     const T L = A::lg2(R2);
@@ -353,12 +354,12 @@ struct MomentUnits {
 };
 
 // Renders a Sersic pixel stored as `raw` at s = R^2 S.
-template <int DT, uint32_t EM>
+template <int DT, uint32_t EM, bool FLOOR>
 __device__ __forceinline__ Px<float> render_moment(const Trial<float>& t, const MomentUnits& mu,
                                                    float raw, float scale, float s2) {
   using A = Arith<float>;
   Px<float> p;
-  const bool floored = s2 < mu.floor;
+  const bool floored = FLOOR && s2 < mu.floor;
   s2 = floored ? mu.floor : s2;
   const float L = A::lg2(s2);
   const float tr = A::ex2(L * mu.ham1);   // t / s
@@ -490,6 +491,20 @@ __device__ __forceinline__ void recombine(const Trial<float>& t, const MomentUni
   }
 }
 
+// Whether no pixel of a stamp of side `side` renders below the model's floor
+// R^2 = 1e-8, so that a sweep need not look: with u the nearest pixel's offset
+// from the centre and e = |(e1, e2)|, R^2 >= |u|^2 (1 - e) / (1 + e) >=
+// |u|^2 (1 - e^2) / 4 at every pixel, asked to be 100 times the floor, while
+// e < 0.996 keeps the FP32 rounding of R^2 (5e-7 ((1 + e) / (1 - e))^2) below an
+// eighth of it.  Not a number: false.
+__device__ __forceinline__ bool clear_of_floor(const Trial<float>& t, int side) {
+  const float last = (float)(side - 1);
+  const float dx = t.x0 - __builtin_amdgcn_fmed3f(__builtin_rintf(t.x0), 0.0f, last);
+  const float dy = t.y0 - __builtin_amdgcn_fmed3f(__builtin_rintf(t.y0), 0.0f, last);
+  const float D = 1.0f - fmaf(t.e1, t.e1, t.e2 * t.e2);
+  return D > 0.008f && fmaf(dx, dx, dy * dy) * D > 4e-6f;
+}
+
 // One sweep: model, residual, Jacobian columns in EM, and their sums.
 // Pixel layouts of a sweep: kLayoutAny walks any side with the lane stride;
 // kLayoutRows is for a wave alone on a stamp whose side divides 64 with at
@@ -519,6 +534,9 @@ constexpr int kSegsMinSide = 65;
 // kLayoutSegsStaged: the same, with the smaller stamps' walk through the LDS
 // buffer of kLayoutStaged (the same sums).
 constexpr int kLayoutSegsStaged = 4;
+// kLayoutSegsOnly: the segments for a stamp known to take them, without the
+// walk's code.
+constexpr int kLayoutSegsOnly = 5;
 
 __host__ __device__ inline constexpr bool rows_layout_fits(int side) {
   return side == 8 || side == 16 || side == 32 || side == 64;
@@ -556,7 +574,8 @@ template <int DT, int LAYOUT>
 __host__ __device__ constexpr bool sums_fused(int side, bool moments) {
   if (LAYOUT == kLayoutRows)
     return (moments || DT == SHAPE_F32) && side * side / kWave % 8 == 0;
-  return (LAYOUT == kLayoutSegs || LAYOUT == kLayoutSegsStaged) && side >= kSegsMinSide;
+  return (LAYOUT == kLayoutSegs || LAYOUT == kLayoutSegsStaged || LAYOUT == kLayoutSegsOnly) &&
+         side >= kSegsMinSide;
 }
 
 // The kinds of sums a sweep forms: J^T J of (x0, y0, e1, e2) among themselves;
@@ -585,15 +604,16 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
   T c2p = (T)0, gp[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) gp[k] = (T)0;
-  // Moment form of the row layout (Sersic with x0, y0, e1, e2 free): along a lane's column the four shape columns are h times polynomials in
-  // u2 of degree 1, 1, 2, 2 with per-column coefficients, J_k = sum_j C_kj
-  // h u2^j.  The lane therefore sums H_j = h u2^j (j = 0..2) against the
-  // other quantities instead of the four columns: M_s = sum h^2 u2^s
-  // (s = 0..4) for the 4 x 4 block, sum H_j v for v = J_Re, J_n, J_I0, 1 and
-  // r, and forms the column sums from them once per sweep -- 22 VALU
-  // operations per pixel where the columns cost 40.
+  // Moment form of the row layout (Sersic with x0, y0, e1, e2 free): along a
+  // lane's column the four shape columns are h times polynomials in u2 of
+  // degree 1, 1, 2, 2 with per-column coefficients, J_k = sum_j C_kj h u2^j.
+  // The lane therefore sums H_j = h u2^j (j = 0..2) against the other
+  // quantities instead of the four columns: M_s = sum h^2 u2^s (s = 0..4) for
+  // the 4 x 4 block, sum H_j v for v = J_Re, J_n, J_I0, 1 and r, and forms the
+  // column sums from them once per sweep -- 22 VALU operations per pixel where
+  // the columns cost 40.
   constexpr bool kMom = MODEL == SHAPE_SERSIC && LAYOUT == kLayoutRows && (EM & 0xFu) == 0xFu;
-  static_assert(MODEL == SHAPE_MOFFAT || sizeof(T) == 4, "the FP64 Sersic sweep is adjoint_sweep's");
+  static_assert(MODEL == SHAPE_MOFFAT || sizeof(T) == 4, "FP64 Sersic: adjoint_sweep.hpp");
   static_assert(LAYOUT == kLayoutAny || (sizeof(T) == 4 && JTJ), "the fit's layouts");
   Moments mom;
   T gq[3] = {(T)0, (T)0, (T)0};
@@ -622,10 +642,11 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
   // FP32 partials instead of being added to them (the same values as adding
   // them to zeros; a compile-time constant where the runs are unrolled)
   // fused: how the columns' own sums round (add_product)
-  auto pixel = [&](auto fused, const float d, const T R2, const T n1, const T n2, const T P2,
-                   const T P3, const bool first = false) {
+  // flr: whether pixels may fall below the model's floor
+  auto pixel = [&](auto fused, auto flr, const float d, const T R2, const T n1, const T n2,
+                   const T P2, const T P3, const bool first = false) {
     constexpr bool kFused = decltype(fused)::value;
-    const Px<T> px = render<DT, MODEL, EM>(t, d, st.scale, R2);
+    const Px<T> px = render<DT, MODEL, EM, decltype(flr)::value>(t, d, st.scale, R2);
     const T m0 = px.m0, h = px.h, r = px.r;
     T J[8];
     if constexpr (MODEL == SHAPE_SERSIC) {
@@ -683,10 +704,10 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     else
       return MomentUnits();
   }();
-  auto mom_pixel = [&](auto fused, const auto& t, const float d, const float u2, const float s2,
-                       const bool first) {
+  auto mom_pixel = [&](auto fused, auto flr, const auto& t, const float d, const float u2,
+                       const float s2, const bool first) {
     constexpr bool kFused = decltype(fused)::value;
-    const Px<float> px = render_moment<DT, EM>(t, mu, d, st.scale, s2);
+    const Px<float> px = render_moment<DT, EM, decltype(flr)::value>(t, mu, d, st.scale, s2);
     const float m0 = px.m0, c = px.c, h = px.h, r = px.r;
     float J[8];
     J[4] = c;
@@ -715,7 +736,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
         if (!(SUMS & (a == 7 ? kSumsProfile : kSumsCross)))
           continue;
         else if (a == 7)
-          mom.Y[j] = j == 0 ? mom.Y[0] + h
+          mom.Y[j] = j == 0 ? add_product<false>(h, 1.0f, h, mom.Y[0])
                             : add_product<kFused>(H[j > 0 ? j - 1 : 0], u2, H[j], mom.Y[j]);
         else
           mom.X[a - 4][j] = A::fma(H[j], J[a], mom.X[a - 4][j]);
@@ -731,6 +752,20 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
       }
     }
   };
+  // A wave alone on its stamp takes a copy of the loops without the floor's
+  // comparison and selections (3 of 55 to 100 VALU per pixel) where no pixel
+  // needs them, nearly always: fit of 262,144 stamps of 64 x 64 FP16 17.7 ->
+  // 17.1 ms.  Not where one LM loop holds the walk and the segments (the two
+  // copies of both spill: 15.4 -> 15.6 ms on 200,000 stamps of mixed sides).
+  constexpr bool kClear = STRIDE == kWave && sizeof(T) == 4 && SUMS == kSumsAll &&
+                          (LAYOUT == kLayoutRows || LAYOUT == kLayoutAny ||
+                           LAYOUT == kLayoutSegsOnly);
+  auto either = [&](auto&& loops) {
+    if constexpr (kClear) {
+      if (clear_of_floor(t, st.side)) return loops(std::false_type());
+    }
+    loops(std::true_type());
+  };
   if constexpr (LAYOUT == kLayoutRows) {
     static_assert(STRIDE == kWave, "the row layout is for a wave alone on its stamp");
     const int lane = tid < 0 ? (int)(threadIdx.x & (kWave - 1)) : tid;
@@ -738,10 +773,8 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     // the lane's column: u1 fixed, the quadratics' per-column coefficients
     const Column<T> col(t, (T)(lane & (sd - 1)) - t.x0);
     const T di = (T)(kWave / sd);
-    T u2 = (T)(lane / sd) - t.y0;
     const int nstep = st.npix / kWave;
     const void* sp = stamp_base<DT>(b, st);
-    uint32_t k = (uint32_t)lane;
     // FP32 stamps in memory, whole runs of kRun rows (sides 32 and 64): the
     // run is unrolled, so its loads issue together and its first pixel opens
     // the partials (2 fewer VALU per pixel); measured on 262,144 64 x 64
@@ -758,54 +791,58 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     const bool blocked = kUnroll && nstep % kRun == 0;   // wave-uniform
     // R^2 S along the column (the moment form's units)
     const T qas = A::uni(t.qa * mu.S), qbs = col.qb * mu.S, qcs = col.qc * mu.S;
-    auto row_pixel = [&](auto fused, const float d, const T u2, const bool first) {
+    auto row_pixel = [&](auto fused, auto flr, const float d, const T u2, const bool first) {
       if constexpr (kMom)
-        mom_pixel(fused, t, d, u2, A::fma(A::fma(qas, u2, qbs), u2, qcs), first);
+        mom_pixel(fused, flr, t, d, u2, A::fma(A::fma(qas, u2, qbs), u2, qcs), first);
       else
-        pixel(fused, d, col.R2(t, u2), col.n1(t, u2), col.n2(t, u2), col.P2(t, u2), col.P3(t, u2),
-              first);
+        pixel(fused, flr, d, col.R2(t, u2), col.n1(t, u2), col.n2(t, u2), col.P2(t, u2),
+              col.P3(t, u2), first);
     };
-    if (blocked) {
+    either([&](auto flr) {
+      T u2 = (T)(lane / sd) - t.y0;
+      uint32_t k = (uint32_t)lane;
+      if (blocked) {
 #pragma unroll 1
-      for (int m0 = 0; m0 < nstep; m0 += kRun) {
+        for (int m0 = 0; m0 < nstep; m0 += kRun) {
 #pragma unroll
-        for (int q = 0; q < kRun; ++q) {
-          row_pixel(RunFused(), load_raw<DT>(sp, k + (uint32_t)(q * kWave)), u2, q == 0);
-          u2 += di;
+          for (int q = 0; q < kRun; ++q) {
+            row_pixel(RunFused(), flr, load_raw<DT>(sp, k + (uint32_t)(q * kWave)), u2, q == 0);
+            u2 += di;
+          }
+          k += (uint32_t)(kRun * kWave);
+          flush();
         }
-        k += (uint32_t)(kRun * kWave);
-        flush();
       }
-    }
-    // The moment form's loop in runs of kRun rows with the run's first pixel
-    // peeled: it opens the FP32 partials, so a flush needs no zeroing.
-    constexpr bool kPeel = SHAPE_ROWS_PEEL && kMom && kFlush == kRun;
-    const bool peeled = kPeel && !blocked && nstep % kRun == 0;   // wave-uniform
-    if (peeled) {
+      // The moment form's loop in runs of kRun rows with the run's first pixel
+      // peeled: it opens the FP32 partials, so a flush needs no zeroing.
+      constexpr bool kPeel = SHAPE_ROWS_PEEL && kMom && kFlush == kRun;
+      const bool peeled = kPeel && !blocked && nstep % kRun == 0;   // wave-uniform
+      if (peeled) {
 #pragma unroll 1
-      for (int m0 = 0; m0 < nstep; m0 += kRun) {
-        row_pixel(std::true_type(), load_raw<DT>(sp, k), u2, true);
-        u2 += di;
-        k += kWave;
-#pragma unroll 1
-        for (int q = 1; q < kRun; ++q) {
-          row_pixel(std::true_type(), load_raw<DT>(sp, k), u2, false);
+        for (int m0 = 0; m0 < nstep; m0 += kRun) {
+          row_pixel(std::true_type(), flr, load_raw<DT>(sp, k), u2, true);
           u2 += di;
           k += kWave;
-        }
-        flush();
-      }
-    }
-    if (!blocked && !peeled) {
 #pragma unroll 1
-      for (int m = 0; m < nstep; ++m) {
-        row_pixel(std::false_type(), load_raw<DT>(sp, k), u2, false);
-        u2 += di;
-        k += kWave;
-        if constexpr (kFlush > 0)
-          if (m % kFlush == kFlush - 1) flush();   // m is wave-uniform
+          for (int q = 1; q < kRun; ++q) {
+            row_pixel(std::true_type(), flr, load_raw<DT>(sp, k), u2, false);
+            u2 += di;
+            k += kWave;
+          }
+          flush();
+        }
       }
-    }
+      if (!blocked && !peeled) {
+#pragma unroll 1
+        for (int m = 0; m < nstep; ++m) {
+          row_pixel(std::false_type(), flr, load_raw<DT>(sp, k), u2, false);
+          u2 += di;
+          k += kWave;
+          if constexpr (kFlush > 0)
+            if (m % kFlush == kFlush - 1) flush();   // m is wave-uniform
+        }
+      }
+    });
     if constexpr (kMom) {
       flush();
       recombine<EM, JTJ, kGrad, (SUMS & kSumsProfile) != 0u, (SUMS & kSumsCross) != 0u,
@@ -813,12 +850,12 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     }
   } else {
     // the lane-stride walk (any side, any team), directly or through LDS
-    auto any_walk = [&]() {
+    auto any_walk = [&](auto flr) {
       int cnt = 0;
       // pixel (i, j) with value d, in the lane-stride order of for_pixels
       auto any_pixel = [&](const float d, int i, int j) {
         const Walk<T> wk(t, (T)j - t.x0, (T)i - t.y0);
-        pixel(std::false_type(), d, wk.R2, wk.n1, wk.n2, wk.P2, wk.P3);
+        pixel(std::false_type(), flr, d, wk.R2, wk.n1, wk.n2, wk.P2, wk.P3);
         if constexpr (kFlush > 0) {
           if (++cnt == kFlush) {
             flush();
@@ -885,7 +922,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
             for (int q = 0; q < kFlush; ++q) {
               if (k0 + q * kWave + t0 < npix) {
                 const Walk<T> wk(t, (T)j - t.x0, (T)i - t.y0);
-                pixel(std::false_type(), d[q], wk.R2, wk.n1, wk.n2, wk.P2, wk.P3);
+                pixel(std::false_type(), flr, d[q], wk.R2, wk.n1, wk.n2, wk.P2, wk.P3);
               }
               i += di;
               j += dj;
@@ -898,48 +935,93 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
           }
           return;
         }
-        for_pixels<STRIDE>(st.side, [&](int k, int i, int j) {
-          any_pixel(load_raw<DT>(sp, (uint32_t)k), i, j);
-        }, tid);
+        if constexpr (kClear) {
+          // Rounds of one pixel per lane in runs of kFlush, each run's first
+          // opening the partials; the coordinates are kept as (exact) floats
+          // and the load's address is the round's: 100 -> 88 VALU per pixel
+          // (65,536 stamps of 48 x 48: fit 6.5 -> 6.1 ms).
+          const int side = st.side, npix = st.npix;
+          const int lane = tid < 0 ? (int)(threadIdx.x & (kWave - 1)) : tid;
+          const int i0 = lane / side, dirow = kWave / side;
+          const float w = (float)side, di = (float)dirow, dj = (float)(kWave - dirow * side);
+          float fi = (float)i0, fj = (float)(lane - i0 * side);
+          using E = typename std::conditional<DT == SHAPE_F32, float, _Float16>::type;
+          const E* row = static_cast<const E*>(sp);
+          auto next = [&](bool first) {
+            const Walk<T> wk(t, fj - t.x0, fi - t.y0);
+            pixel(std::false_type(), flr, (float)row[lane], wk.R2, wk.n1, wk.n2, wk.P2, wk.P3,
+                  first);
+          };
+          auto step = [&] {
+            row += kWave;
+            fj += dj;
+            const bool wrap = fj >= w;
+            fi += wrap ? di + 1.0f : di;
+            fj = wrap ? fj - w : fj;
+          };
+          const int runs = npix / (kFlush * kWave);
+#pragma unroll 1
+          for (int m = 0; m < runs; ++m) {
+            next(true);
+            step();
+#pragma unroll 1
+            for (int q = 1; q < kFlush; ++q) {
+              next(false);
+              step();
+            }
+            flush();
+          }
+#pragma unroll 1
+          for (int k = runs * kFlush * kWave; k < npix; k += kWave) {
+            if (k + lane < npix) next(false);
+            step();
+          }
+        } else {
+          for_pixels<STRIDE>(st.side, [&](int k, int i, int j) {
+            any_pixel(load_raw<DT>(sp, (uint32_t)k), i, j);
+          }, tid);
+        }
       }
-  
     };
-    if constexpr (LAYOUT == kLayoutSegs || LAYOUT == kLayoutSegsStaged) {
+    if constexpr (LAYOUT == kLayoutSegs || LAYOUT == kLayoutSegsStaged ||
+                  LAYOUT == kLayoutSegsOnly) {
       static_assert(STRIDE == kWave, "the segment layout is for a wave alone on its stamp");
-      if (st.side >= kSegsMinSide) {
+      if (LAYOUT == kLayoutSegsOnly || st.side >= kSegsMinSide) {
         const int lane = tid < 0 ? (int)(threadIdx.x & (kWave - 1)) : tid;
         const int W = st.side, last = W - 1;
         const int S = W * ((W + kSegRows - 1) / kSegRows);   // segments
         const void* sp = stamp_base<DT>(b, st);
+        either([&](auto flr) {
 #pragma unroll 1
-        for (int s0 = 0; s0 < S; s0 += kWave) {   // wave-uniform
-          const int sg = s0 + lane;
-          const bool on = sg < S;
-          const int g = on ? sg / W : 0, j = on ? sg - g * W : 0, r0 = g * kSegRows;
-          const Column<T> col(t, (T)j - t.x0);
-          // the segment's pixels (rows past the stamp read its last row and are
-          // skipped below), loaded back to back
-          float d[kSegRows];
+          for (int s0 = 0; s0 < S; s0 += kWave) {   // wave-uniform
+            const int sg = s0 + lane;
+            const bool on = sg < S;
+            const int g = on ? sg / W : 0, j = on ? sg - g * W : 0, r0 = g * kSegRows;
+            const Column<T> col(t, (T)j - t.x0);
+            // the segment's pixels (rows past the stamp read its last row and are
+            // skipped below), loaded back to back
+            float d[kSegRows];
 #pragma unroll
-          for (int q = 0; q < kSegRows; ++q) {
-            const int i = r0 + q < last ? r0 + q : last;
-            d[q] = load_raw<DT>(sp, (uint32_t)(i * W + j));
-          }
-#pragma unroll
-          for (int q = 0; q < kSegRows; ++q) {
-            if (on && r0 + q < W) {
-              const T u2 = (T)(r0 + q) - t.y0;
-              pixel(std::true_type(), d[q], col.R2(t, u2), col.n1(t, u2), col.n2(t, u2),
-                    col.P2(t, u2), col.P3(t, u2));
+            for (int q = 0; q < kSegRows; ++q) {
+              const int i = r0 + q < last ? r0 + q : last;
+              d[q] = load_raw<DT>(sp, (uint32_t)(i * W + j));
             }
+#pragma unroll
+            for (int q = 0; q < kSegRows; ++q) {
+              if (on && r0 + q < W) {
+                const T u2 = (T)(r0 + q) - t.y0;
+                pixel(std::true_type(), flr, d[q], col.R2(t, u2), col.n1(t, u2), col.n2(t, u2),
+                      col.P2(t, u2), col.P3(t, u2));
+              }
+            }
+            flush();   // one partial per segment
           }
-          flush();   // one partial per segment
-        }
+        });
       } else {
-        any_walk();
+        either(any_walk);
       }
     } else {
-      any_walk();
+      either(any_walk);
     }
   }
   flush();

@@ -121,3 +121,27 @@ def test_split_fit_of_mixed_sides_and_models(shape, storage):
     db.sigma[10] = -1.0
     db.pixels[int(b.offsets[11])] = float("nan")
     _same_fits(shape, db, _repeat(shape, db, SPLIT_LIMIT + 1), shape.default_opts())
+
+
+# The one-wave fit drops the model's floor from its sweeps where no pixel can
+# reach it; the four-wave fit never does.  Centres on a pixel, near one, half way
+# and outside, ellipticities up to the bound, by starting point.
+@pytest.mark.parametrize("side", [16, 33, 48, 64, 72])
+def test_sweep_without_floor_equals_sweep_with_it(shape, side):
+    import torch
+    small, large = _one_side(shape, side, "f32", 0)
+    rng = np.random.default_rng(side)
+    p = np.empty((24, 8), np.float32)
+    p[:, 0] = side // 2 + np.tile([0.0, 1e-4, 1e-3, 0.01, 0.5, -side], 4)
+    p[:, 1] = side // 2 + np.repeat([0.0, 1e-4, 0.3, 0.5], 6)
+    e = np.repeat([0.0, 0.5, 0.99, 0.997], 6)
+    th = rng.uniform(0, 2 * np.pi, 24)
+    p[:, 2], p[:, 3] = e * np.cos(th), e * np.sin(th)
+    p[:, 4:] = [0.15 * side, 2.0, 50.0, 10.0]
+    got = []
+    for batch in (small, large):
+        t = torch.from_numpy(np.tile(p, (batch.n // 24, 1))).cuda()
+        f = shape.fit_sersic(batch, p_init=t, opts=shape.default_opts(max_iter_lm=2), want_perr=True)
+        got.append({k: v[:24].cpu().numpy() for k, v in f.items()})
+    for k in got[0]:
+        np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
