@@ -9,6 +9,14 @@
 // stamp, pixel l + 64 m in slot m of lane l), centroid_any_kernel for any
 // side (a SlotMap column layout; one wave per stamp up to side 64, a team of
 // three or four waves above).
+//
+// Bound by VALU issue (4.1 cycles per instruction of a SIMD; LDS atomics, one
+// per pixel, take a tenth of the time): per pixel about 2 instructions for the
+// extremes, 13 for its ring, 3 per step of the iteration; per step 110 more.
+// With the ring from an integer square root with two corrections, the brightest
+// pixel's index carried along and the border's selects on every pixel, 262,144
+// stamps of 64 x 64 FP16 took 1.86 ms, now 1.57; 100,000 of 48 x 48 854 -> 744 us;
+// 200,000 of mixed sides 3.30 -> 2.92 ms; 1,048,576 of 32 x 32 2.48 -> 2.29 ms.
 #include "slots.hpp"
 #include "kernels.hpp"
 
@@ -17,15 +25,13 @@ namespace {
 
 constexpr int kMaxRings = 184;  // ring index of a 128-px stamp is at most 180
 
-// Smallest r >= 0 with r * r >= d2 (the ring holding a pixel at distance^2
-// d2), for 0 <= d2 < 2^16.  The hardware square root is within an ulp, and a
-// non-square d2 lies at least 1 / 512 from the nearest square root, so the
-// ceiling can only be off at a perfect square, and then by one.
-__device__ inline int ring_of(int d2) {
-  int r = (int)ceilf(__builtin_amdgcn_sqrtf((float)d2));
-  r += __mul24(r, r) < d2;
-  r -= (r > 0 && __mul24(r - 1, r - 1) >= d2);
-  return r;
+// The ring of a pixel at squared distance d2 from the centre: the smallest r
+// with r * r >= d2, from t = d2 - 1/2 (exact in FP32), 0 <= d2 < 2^16.
+// sqrt(t) is at least 1 / 1024 away from every integer, farther than the
+// hardware square root's error, so its ceiling is r.  The centre's own pixel
+// (d2 = 0) comes out in ring 1, which spans [0, 1] anyway.
+__device__ __forceinline__ int ring_of(float t) {
+  return (int)ceilf(__builtin_amdgcn_sqrtf(fabsf(t)));
 }
 
 // 1.5 * 2^52: adding it to a double of magnitude below 2^51 rounds that value
@@ -38,20 +44,33 @@ constexpr double kRoundMagic = 6755399441055744.0;
 // ring sums are then exact and do not depend on the order lanes add in.
 struct FixedPoint {
   double fix, kofs;
-  long long magic_bits;
   __device__ FixedPoint(double amax, double sky0, int npix) {
     const double fmaxabs = amax + fabs(sky0) + 1.0;
     fix = ldexp(1.0, ilogb(fmin(2.3e18 / (double)npix, 0x1p50) / fmaxabs));
     // (I - sky0) fix + magic in one FMA: fix * I + (magic - sky0 fix)
     kofs = kRoundMagic - sky0 * fix;
-    magic_bits = __builtin_bit_cast(long long, kRoundMagic);
   }
-  __device__ __forceinline__ void deposit(unsigned long long* ring, float v, int d2) const {
-    const double t = fma((double)v, fix, kofs);
-    const long long q = __builtin_bit_cast(long long, t) - magic_bits;
-    atomicAdd(&ring[ring_of(d2)], (unsigned long long)q);
+  // t: the pixel's d2 - 1/2
+  __device__ __forceinline__ void deposit(unsigned long long* ring, float v, float t) const {
+    const uint64_t w = __builtin_bit_cast(uint64_t, fma((double)v, fix, kofs));
+    // less the bits of kRoundMagic, whose low word is 0
+    const uint32_t hi = (uint32_t)(w >> 32) - 0x43380000u;
+    atomicAdd(&ring[ring_of(t)], (unsigned long long)(((uint64_t)hi << 32) | (uint32_t)w));
   }
 };
+
+// Largest value, largest |value| and whether any is not a number, over N
+// values (an infinity shows in amax): three instructions for two values.
+template <int N>
+__device__ __forceinline__ void extremes(const float (&v)[N], int m0, int m1, float& best,
+                                         float& amax, bool& nan) {
+#pragma unroll
+  for (int m = m0; m < m1; m += 2) {
+    best = fmaxf(best, fmaxf(v[m], v[m + 1]));
+    amax = fmaxf(amax, fmaxf(fabsf(v[m]), fabsf(v[m + 1])));
+    nan |= __builtin_isunordered(v[m], v[m + 1]);
+  }
+}
 
 // r50: the first ring r >= 1 where the cumulative fixed-point flux reaches
 // half the total, interpolated linearly over [r - 1, r] (rings 0 and 1
@@ -167,21 +186,16 @@ __global__ __launch_bounds__(kWave, SHAPE_CENTROID_WAVES_PER_SIMD) void centroid
 
     // Pass 1: finiteness, border sum, brightest pixel, largest |I|.
     double border = 0.0;
-    float best = -__builtin_huge_valf();
-    int besti = 0x7fffffff;
-    bool nonfinite = false;
-    float vmin = __builtin_huge_valf();
-#pragma unroll
-    for (int m = 0; m < kSlots; ++m) {
-      const float v = px.v[m];
-      nonfinite |= !__builtin_isfinite(v);
-      if (v > best) {  // the index increases with m, so ties keep the lowest
-        best = v;
-        besti = lane + kWave * m;
-      }
-      vmin = fminf(vmin, v);
+    float best = -__builtin_huge_valf(), amax = 0.0f;
+    bool nan = false;
+    static_assert(kSlots == 1 || kSlots % 2 == 0, "slots in pairs");
+    if constexpr (kSlots == 1) {
+      best = px.v[0];
+      amax = fabsf(best);
+      nan = __builtin_isnan(best);
+    } else {
+      extremes(px.v, 0, kSlots, best, amax, nan);
     }
-    float amax = fmaxf(fabsf(best), fabsf(vmin));  // max |I| = max(max I, -min I)
     // the border: whole columns 0 and W - 1, the rest of rows 0 and W - 1
     if (jl == 0 || jl == SIDE - 1) {
 #pragma unroll
@@ -190,31 +204,36 @@ __global__ __launch_bounds__(kWave, SHAPE_CENTROID_WAVES_PER_SIMD) void centroid
       if (il == 0) border += (double)px.v[0];
       if (il == kR - 1) border += (double)px.v[kSlots - 1];
     }
-    if (wave_any(nonfinite)) {
+    if (wave_any(nan || !__builtin_isfinite(amax))) {
       write_failed(out, lane, iters, status, s, SHAPE_ST_NONFINITE_INPUT);
       continue;
     }
     border = wave_sum(border);
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) {
-      float ov = __shfl_xor(best, m, kWave);
-      int oi = __shfl_xor(besti, m, kWave);
-      if (ov > best || (ov == best && oi < besti)) {
-        best = ov;
-        besti = oi;
-      }
+      best = fmaxf(best, __shfl_xor(best, m, kWave));
       amax = fmaxf(amax, __shfl_xor(amax, m, kWave));
+    }
+    // the lowest index that holds it: pixels ascend with the slot, then the lane
+    int besti = 0;
+#pragma unroll
+    for (int m = 0; m < kSlots; ++m) {
+      const uint64_t at = __ballot(px.v[m] == best);
+      if (at) {
+        besti = kWave * m + __builtin_ctzll(at);
+        break;
+      }
     }
     const double sky0 = border / (4.0 * W - 4.0);
     const int i0 = besti / W, j0 = besti - (besti / W) * W;
 
     // Pass 2: ring sums of f = I - sky0 about the brightest pixel.
-    const int nrings = ring_of(2 * (W - 1) * (W - 1)) + 1;
+    const int nrings = ring_of((float)(2 * (W - 1) * (W - 1)) - 0.5f) + 1;
     const FixedPoint fp((double)amax, sky0, st.npix);
     for (int r = lane; r < nrings; r += kWave) ring[r] = 0ull;
     __syncthreads();
     {
-      const int dj2 = __mul24(jl - j0, jl - j0);
+      const float dj = (float)(jl - j0), di0 = (float)(il - i0), tj = fmaf(dj, dj, -0.5f);
       constexpr int kGrp = kSlots < 8 ? kSlots : 8;
 #pragma unroll
       for (int m0 = 0; m0 < kSlots; m0 += kGrp) {
@@ -230,8 +249,8 @@ __global__ __launch_bounds__(kWave, SHAPE_CENTROID_WAVES_PER_SIMD) void centroid
                      : "memory");
 #pragma unroll
         for (int q = 0; q < kGrp; ++q) {
-          const int di = il + kR * (m0 + q) - i0;
-          fp.deposit(ring, v[q], __mul24(di, di) + dj2);
+          const float di = di0 + (float)(kR * (m0 + q));
+          fp.deposit(ring, v[q], fmaf(di, di, tj));
         }
       }
     }
@@ -316,7 +335,6 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
   __shared__ unsigned long long ring[2 * kPairRings];
   __shared__ float wy_row[2 * W];
   const int lane = threadIdx.x, g = lane >> 5, jl = lane & (W - 1);
-  const bool hi = g != 0;
   for (int64_t s0 = 2 * (int64_t)blockIdx.x; s0 < b.n; s0 += 2 * (int64_t)gridDim.x) {
     const int64_t s = s0 + g < b.n ? s0 + g : s0;   // a missing second stamp repeats the first
     const bool own = s0 + g < b.n;                  // and writes nothing
@@ -332,19 +350,10 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
     }
     // Pass 1: finiteness, border sum, brightest pixel, largest |I|.
     double border = 0.0;
-    float best = -__builtin_huge_valf(), vmin = __builtin_huge_valf();
-    int besti = 0x7fffffff;
-    bool nonfinite = false;
-#pragma unroll
-    for (int m = 0; m < kSlots; ++m) {
-      nonfinite |= !__builtin_isfinite(v[m]);
-      if (v[m] > best) {  // the index increases with m, so ties keep the lowest
-        best = v[m];
-        besti = m * W + jl;
-      }
-      vmin = fminf(vmin, v[m]);
-    }
-    float amax = fmaxf(fabsf(best), fabsf(vmin));
+    float best = -__builtin_huge_valf(), amax = 0.0f;
+    bool nan = false;
+    extremes(v, 0, kSlots, best, amax, nan);
+    const bool nonfinite = nan || !__builtin_isfinite(amax);
     if (jl == 0 || jl == W - 1) {
 #pragma unroll
       for (int m = 0; m < kSlots; ++m) border += (double)v[m];
@@ -353,14 +362,17 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
     }
 #pragma unroll
     for (int m = 16; m >= 1; m >>= 1) {
-      const float ov = __shfl_xor(best, m, kWave);
-      const int oi = __shfl_xor(besti, m, kWave);
-      if (ov > best || (ov == best && oi < besti)) {
-        best = ov;
-        besti = oi;
-      }
+      best = fmaxf(best, __shfl_xor(best, m, kWave));
       amax = fmaxf(amax, __shfl_xor(amax, m, kWave));
     }
+    // the lowest index that holds it (a lane's lowest row, then over the half)
+    int besti = 0x7fff;
+#pragma unroll
+    for (int m = kSlots - 1; m >= 0; --m) besti = v[m] == best ? m * W : besti;
+    besti = besti == 0x7fff ? besti : besti + jl;
+#pragma unroll
+    for (int m = 16; m >= 1; m >>= 1) besti = min(besti, __shfl_xor(besti, m, kWave));
+    besti &= W * W - 1;   // a stamp that holds NaN alone has none
     {
       double bu[2] = {border, 0.0};
       half_sum_n(bu);
@@ -378,7 +390,7 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
     for (int r = jl; r < kPairRings; r += W) rg[r] = 0ull;
     __syncthreads();
     if (live) {
-      const int dj2 = __mul24(jl - j0, jl - j0);
+      const float dj = (float)(jl - j0), i0f = (float)i0, tj = fmaf(dj, dj, -0.5f);
 #pragma unroll
       for (int m0 = 0; m0 < kSlots; m0 += 8) {
         float w8[8];
@@ -390,8 +402,8 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
                      : "memory");
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          const int di = m0 + q - i0;
-          fp.deposit(rg, w8[q], __mul24(di, di) + dj2);
+          const float di = (float)(m0 + q) - i0f;
+          fp.deposit(rg, w8[q], fmaf(di, di, tj));
         }
       }
     }
@@ -512,33 +524,37 @@ __device__ __forceinline__ void centroid_any(const shape_batch& b, const KOpts& 
 
   // Pass 1: finiteness, border sum, brightest pixel (lowest index on ties),
   // largest |I|, over the pixels of the stamp.
+  // A slot that is no pixel repeats the column's last row (load_slots), so it
+  // matters to the border sum alone; only slot rows - 1 can be one (or all of
+  // a lane that is off), so the blocks below it are summed unasked.
   double border = 0.0;
-  float best = -__builtin_huge_valf(), amax = 0.0f;
-  int besti = 0x7fffffff;
-  bool nonfinite = false;
-  {
-    const bool bcol = jl == 0 || jl == W - 1;
+  float best = -__builtin_huge_valf(), amax = 0.0f, last = 0.0f;
+  bool nan = false;
+  const bool bcol = jl == 0 || jl == W - 1;
 #pragma unroll
-    for (int m0 = 0; m0 < K; m0 += kColumnBlock) {
-      if (m0 < rows) {
+  for (int m0 = 0; m0 < K; m0 += kColumnBlock) {
+    if (m0 < rows) {
+      extremes(v, m0, m0 + kColumnBlock, best, amax, nan);
+      if (m0 + kColumnBlock < rows) {
+        if (bcol) {
+#pragma unroll
+          for (int m = m0; m < m0 + kColumnBlock; ++m) border += (double)v[m];
+        }
+      } else {
 #pragma unroll
         for (int m = m0; m < m0 + kColumnBlock; ++m) {
-          // selects, not branches: a slot outside the stamp changes nothing
-          const bool ok = mp.valid(m);
-          const float x = v[m];
-          const int i = mp.row(m);
-          nonfinite |= ok && !__builtin_isfinite(x);
-          const float xb = ok ? x : -__builtin_huge_valf();
-          if (xb > best) {  // a lane's index increases with m
-            best = xb;
-            besti = i * W + jl;
-          }
-          amax = fmaxf(amax, ok ? fabsf(x) : 0.0f);
-          border += (ok && (bcol || i == 0 || i == W - 1)) ? (double)x : 0.0;
+          if (bcol) border += mp.valid(m) ? (double)v[m] : 0.0;
+          last = m == rows - 1 ? v[m] : last;
         }
       }
     }
   }
+  if (!bcol) {   // rows 0 and W - 1
+    border = il == 0 ? (double)v[0] : 0.0;
+    border += mp.row(rows - 1) == W - 1 ? (double)last : 0.0;
+  }
+  border = mp.on ? border : 0.0;
+  const bool nonfinite = nan || !__builtin_isfinite(amax);
   const bool bad = TEAM > 1 ? false : wave_any(nonfinite);
   if (TEAM == 1 && bad) {
     write_failed(out, t, iters, status, s, SHAPE_ST_NONFINITE_INPUT);
@@ -547,13 +563,30 @@ __device__ __forceinline__ void centroid_any(const shape_batch& b, const KOpts& 
   border = wave_sum(border);
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) {
-    const float ov = __shfl_xor(best, m, kWave);
-    const int oi = __shfl_xor(besti, m, kWave);
-    if (ov > best || (ov == best && oi < besti)) {
-      best = ov;
-      besti = oi;
-    }
+    best = fmaxf(best, __shfl_xor(best, m, kWave));
     amax = fmaxf(amax, __shfl_xor(amax, m, kWave));
+  }
+  // The lowest index that holds it: slot m of thread t is pixel t + R W m, so
+  // pixels ascend with the slot, then the lane (a repeated last row comes after
+  // its pixel; lanes that are off are left out).
+  int besti = 0x7fffffff;
+  {
+    const uint64_t on = __ballot(mp.on);
+    bool found = false;
+#pragma unroll
+    for (int m0 = 0; m0 < K; m0 += kColumnBlock) {
+      if (m0 < rows && !found) {
+#pragma unroll
+        for (int m = m0; m < m0 + kColumnBlock; ++m) {
+          const uint64_t at = __ballot(v[m] == best) & on;
+          if (at) {
+            besti = (t & ~(kWave - 1)) + __builtin_ctzll(at) + R * W * m;
+            found = true;
+            break;
+          }
+        }
+      }
+    }
   }
   if constexpr (TEAM > 1) {
     const int nf = wave_any(nonfinite) ? 1 : 0;
@@ -586,12 +619,13 @@ __device__ __forceinline__ void centroid_any(const shape_batch& b, const KOpts& 
   const int i0 = besti / W, j0 = besti - (besti / W) * W;
 
   // Pass 2: ring sums of f = I - sky0 about the brightest pixel.
-  const int nrings = ring_of(2 * (W - 1) * (W - 1)) + 1;
+  const int nrings = ring_of((float)(2 * (W - 1) * (W - 1)) - 0.5f) + 1;
   const FixedPoint fp((double)amax, sky0, st.npix);
   for (int r = t; r < nrings; r += kWave * TEAM) sh.ring[r] = 0ull;
   __syncthreads();
   {
-    const int dj2 = __mul24(jl - j0, jl - j0);
+    const float dj = (float)(jl - j0), di0 = (float)(il - i0), tj = fmaf(dj, dj, -0.5f);
+    const float Rf = (float)R;
 #pragma unroll
     for (int m0 = 0; m0 < K; m0 += kColumnBlock) {
       if (m0 < rows) {
@@ -605,8 +639,8 @@ __device__ __forceinline__ void centroid_any(const shape_batch& b, const KOpts& 
 #pragma unroll
         for (int q = 0; q < kColumnBlock; ++q) {
           const int m = m0 + q;
-          const int di = mp.row(m) - i0;
-          if (mp.valid(m)) fp.deposit(sh.ring, g[q], __mul24(di, di) + dj2);
+          const float di = fmaf(Rf, (float)m, di0);
+          if (mp.valid(m)) fp.deposit(sh.ring, g[q], fmaf(di, di, tj));
         }
       }
     }

@@ -145,3 +145,46 @@ def test_sweep_without_floor_equals_sweep_with_it(shape, side):
         got.append({k: v[:24].cpu().numpy() for k, v in f.items()})
     for k in got[0]:
         np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("side", [4, 5, 8, 16, 17, 22, 31, 32, 33, 48, 63, 64, 65, 96, 97, 128])
+def test_centroid_start_is_the_first_maximum(shape, side, storage):
+    """The start before any step: the lowest index among equal maxima, and r50 of
+    the growth curve about it (rings ceil(distance), ring 0 within ring 1)."""
+    import torch
+    rng = np.random.default_rng(side)
+    n = 12
+    img = rng.integers(0, 4, (n, side, side)).astype(np.float32)   # many equal maxima
+    img[0] = 1.0                                                   # nothing above the border
+    img[1:5] *= -1.0
+    for k, (i, j) in enumerate([(0, 0), (0, side - 1), (side - 1, 0), (side - 1, side - 1)]):
+        img[5 + k, i, j] = 9.0
+    img[9, side // 2:] = 9.0                                       # whole rows
+    img[10, -1, -1], img[11, 0, 0] = np.nan, -np.inf
+    pix = torch.from_numpy(img.astype(np.float16) if storage == "f16" else img).cuda().reshape(-1)
+    db = shape.DeviceBatch(pixels=pix, sigma=torch.ones(n, device="cuda"), side0=side,
+                           scale=torch.ones(n, device="cuda") if storage == "f16" else None)
+    rec, it, st = (t.cpu().numpy() for t in shape.centroid(db, shape.default_opts(max_iter_centroid=0)))
+    assert (st[10:] == shape.ST_NONFINITE_INPUT).all() and np.isnan(rec[10:]).all()
+    assert (it == 0).all()
+    ii, jj = np.mgrid[:side, :side]
+    for s in range(10):
+        a = img[s].astype(np.float64)
+        i0, j0 = divmod(int(np.argmax(a)), side)
+        assert (rec[s, 0], rec[s, 1]) == (j0, i0), s   # x0, y0; 5 is r50, 7 the flux
+        edge = np.concatenate([a[0], a[-1], a[1:-1, 0], a[1:-1, -1]])
+        f = a - edge.sum() / (4.0 * side - 4.0)
+        ring = np.ceil(np.sqrt((ii - i0) ** 2 + (jj - j0) ** 2)).astype(int)
+        c = np.cumsum(np.bincount(ring.ravel(), weights=f.ravel()))
+        if abs(c[-1]) < 1e-9 * np.abs(f).sum() + 1e-9:
+            continue   # the total's sign is its rounding's
+        if c[-1] < 0:
+            assert st[s] & shape.ST_NONPOSITIVE_FLUX
+            continue
+        r = int(np.argmax((2 * c >= c[-1]) & (np.arange(len(c)) >= 1)))
+        before = 0.0 if r == 1 else c[r - 1]
+        want = (r - 1) + (0.5 * c[-1] - before) / (c[r] - before)
+        # FP64 sums of up to 2^14 terms against an exact total, then FP32
+        np.testing.assert_allclose(rec[s, 5], want, rtol=1e-6, atol=1e-6)
+        np.testing.assert_allclose(rec[s, 7], c[-1], rtol=1e-6)
