@@ -334,6 +334,7 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
   constexpr int W = kPairSide, kSlots = kPairSide;
   __shared__ unsigned long long ring[2 * kPairRings];
   __shared__ float wy_row[2 * W];
+  __shared__ __align__(16) double part[8];
   const int lane = threadIdx.x, g = lane >> 5, jl = lane & (W - 1);
   for (int64_t s0 = 2 * (int64_t)blockIdx.x; s0 < b.n; s0 += 2 * (int64_t)gridDim.x) {
     const int64_t s = s0 + g < b.n ? s0 + g : s0;   // a missing second stamp repeats the first
@@ -375,7 +376,7 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
     besti &= W * W - 1;   // a stamp that holds NaN alone has none
     {
       double bu[2] = {border, 0.0};
-      half_sum_n(bu);
+      half_sum_n(bu, part);
       border = bu[0];
     }
     uint32_t stt = st.bad ? st.bad : (half_any(nonfinite) ? SHAPE_ST_NONFINITE_INPUT : 0u);
@@ -480,7 +481,7 @@ __global__ __launch_bounds__(kWave, 5) void centroid_pair_kernel(shape_batch b, 
       const double wx = (double)fast_exp2(-(t1 * t1) * c2);
       const double dl = (double)kC - y;
       double u[4] = {wx * s0d, wx * (double)t1 * s0d, wx * (dl * s0d + s1d), 0.0};
-      half_sum_n(u);
+      half_sum_n(u, part);
       if (!done) {
         ++it;
         done = centroid_step(u[0], u[1], u[2], x, y, W, o, stt);

@@ -166,12 +166,11 @@ __device__ __forceinline__ void swap_add16(double& a, double& b) {
   a = pair_to_double(x0, x1) + pair_to_double(y0, y1);
 }
 
-// Sums of N FP64 values (N a multiple of 4) over the wave, every lane
-// receiving all N: two halving steps (row k then carries entries
-// kN/4 .. kN/4 + N/4 - 1), a scan within each row of 16, and the row totals
-// read back from lanes 15, 31, 47 and 63.
+// Sums of N FP64 values (N a multiple of 4) over the wave: two halving steps
+// (row k then carries entries kN/4 .. kN/4 + N/4 - 1) and a scan within each
+// row of 16, which leaves entry kN/4 + j in u[j] of lane 16 k + 15.
 template <int N>
-__device__ inline void wave_sum_n(double (&u)[N]) {
+__device__ __forceinline__ void wave_rows_n(double (&u)[N]) {
   static_assert(N % 4 == 0, "N must be a multiple of 4");
   constexpr int H = N / 2, Q = N / 4;
 #pragma unroll
@@ -185,6 +184,25 @@ __device__ inline void wave_sum_n(double (&u)[N]) {
     u[j] = dpp::add<dpp::kShr4, 0xf>(u[j]);
     u[j] = dpp::add<dpp::kShr8, 0xf>(u[j]);
   }
+}
+
+// Those totals stored to dst[0 .. N - 1].
+template <int N>
+__device__ __forceinline__ void store_rows(const double (&u)[N], double* dst) {
+  constexpr int Q = N / 4;
+  const int lane = threadIdx.x & (kWave - 1);
+  if ((lane & 15) == 15) {
+#pragma unroll
+    for (int j = 0; j < Q; ++j) dst[Q * (lane >> 4) + j] = u[j];
+  }
+}
+
+// The wave sums, every lane receiving all N: read back from the rows' last
+// lanes.
+template <int N>
+__device__ inline void wave_sum_n(double (&u)[N]) {
+  constexpr int Q = N / 4;
+  wave_rows_n(u);
   double t[N];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {

@@ -345,7 +345,9 @@ __global__ __launch_bounds__(kWave, SHAPE_MOMENTS_WAVES_PER_SIMD) void moments_k
 // Two 32 x 32 stamps per wave (lanes 32 g + j: column j of stamp g, slot m =
 // row m), as centroid_pair_kernel: the moments and the step of
 // moments_kernel with the sums taken per half-wave, iterating until both
-// stamps stop.
+// stamps stop.  (The totals come by readlanes: through LDS it ran 3% faster,
+// but the compiler then fused the step's FP64 algebra differently, and where
+// an iteration does not converge its last bits grow into other results.)
 template <int DT>
 __global__ __launch_bounds__(kWave, SHAPE_MOMENTS_WAVES_PER_SIMD) void moments_pair_kernel(
     shape_batch b, KOpts o, const float* rec_in, float* rec_out, int32_t* iters,
@@ -469,13 +471,13 @@ __device__ __forceinline__ void moments_any(const shape_batch& b, const KOpts& o
       // The step's FP64 algebra runs on one wave of the team (the leader,
       // chosen by the stamp index so the leaders of different workgroups
       // fall on different SIMDs); the others wait for its new state.
-      wave_sum_n(u);
+      // Each wave's totals go to LDS from the lanes that hold them (read back
+      // to one lane first: 200,000 stamps of mixed sides, teams of three 1,643
+      // -> 1,550 us, of four 1,673 -> 1,601).
       const int w = t / kWave, lane = t & (kWave - 1);
       double* b = part + parity * TEAM * 12;
-      if (lane == 0) {
-#pragma unroll
-        for (int j = 0; j < 12; ++j) b[w * 12 + j] = u[j];
-      }
+      wave_rows_n(u);
+      store_rows(u, b + w * 12);
       __syncthreads();
       if (w == (int)(s % TEAM)) {
 #pragma unroll
@@ -534,7 +536,7 @@ template <int DT, int TEAM>
 __global__ __launch_bounds__(kWave * TEAM, SHAPE_MOMENTS_ANY_WAVES_PER_SIMD) void
 moments_any_kernel(shape_batch b, KOpts o, const float* rec_in, float* rec_out, int32_t* iters,
                    uint32_t* status, int take_bad, int chunk) {
-  __shared__ double part[2 * TEAM * 12];
+  __shared__ __align__(16) double part[2 * TEAM * 12];
   __shared__ StepShare share[2];
   int parity = 0;
   const int t = threadIdx.x;
@@ -564,7 +566,7 @@ template <int DT>
 __global__ __launch_bounds__(4 * kWave, SHAPE_MOMENTS_ANY_WAVES_PER_SIMD) void
 moments_mixed_kernel(shape_batch b, KOpts o, const float* rec_in, float* rec_out, int32_t* iters,
                      uint32_t* status) {
-  __shared__ double part[2 * 4 * 12];
+  __shared__ __align__(16) double part[2 * 4 * 12];
   __shared__ StepShare share[2];
   const int64_t s = blockIdx.x;   // the grid is b.n
   const int t = threadIdx.x, w = __builtin_amdgcn_readfirstlane(t / kWave);

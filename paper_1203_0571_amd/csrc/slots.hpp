@@ -98,14 +98,13 @@ __device__ __forceinline__ void load_slots(float (&v)[K], const void* sp, const 
 // fast wave's next write off the half a slow wave still reads.
 template <int TEAM, int N>
 __device__ __forceinline__ void team_sum_n(double (&u)[N], double* buf, int& parity) {
-  wave_sum_n(u);
-  if constexpr (TEAM > 1) {
-    const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  if constexpr (TEAM == 1) {
+    wave_sum_n(u);
+  } else {
+    const int w = threadIdx.x / kWave;
     double* b = buf + parity * TEAM * N;
-    if (lane == 0) {
-#pragma unroll
-      for (int j = 0; j < N; ++j) b[w * N + j] = u[j];
-    }
+    wave_rows_n(u);
+    store_rows(u, b + w * N);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < N; ++j) {
@@ -172,13 +171,12 @@ __device__ __forceinline__ void team_sync() {
 // forms are shared by two stamps.
 constexpr int kPairSide = 32;
 
-// Sums of N FP64 values (N even) within each half-wave, every lane receiving
-// its half's N totals: v_permlane16_swap halves the values between the rows
-// of a half (rows 0 and 2 then carry entries 0..N/2-1, rows 1 and 3 the
-// rest), a scan within each row of 16 finishes them, and the totals are read
-// from lanes 15, 31 (first half) and 47, 63 (second half).
+// Sums of N FP64 values (N even) within each half-wave: v_permlane16_swap
+// halves the values between the rows of a half (rows 0 and 2 then carry
+// entries 0..N/2-1, rows 1 and 3 the rest), and a scan within each row of 16
+// leaves the totals in the rows' last lanes.
 template <int N>
-__device__ inline void half_sum_n(double (&u)[N]) {
+__device__ __forceinline__ void half_rows_n(double (&u)[N]) {
   static_assert(N % 2 == 0, "N must be even");
   constexpr int H = N / 2;
 #pragma unroll
@@ -190,6 +188,14 @@ __device__ inline void half_sum_n(double (&u)[N]) {
     u[j] = dpp::add<dpp::kShr4, 0xf>(u[j]);
     u[j] = dpp::add<dpp::kShr8, 0xf>(u[j]);
   }
+}
+
+// Every lane receiving its half's N totals, read from lanes 15, 31 (first
+// half) and 47, 63 (second half).
+template <int N>
+__device__ inline void half_sum_n(double (&u)[N]) {
+  constexpr int H = N / 2;
+  half_rows_n(u);
   const bool hi = (threadIdx.x & (kWave - 1)) >= 32;
   double t[N];
 #pragma unroll
@@ -201,7 +207,27 @@ __device__ inline void half_sum_n(double (&u)[N]) {
   for (int j = 0; j < N; ++j) u[j] = t[j];
 }
 
-// The same for N FP32 values.
+// The same through LDS (buf: 2 N doubles): picked by readlanes they take 6 N
+// VALU instructions, the unit these iterations saturate (centroid of 1,048,576
+// stamps of 32 x 32 2.29 -> 2.17 ms).  A whole wave's sums take 2 N readlanes
+// and were faster that way (262,144 stamps of 64 x 64: 1.57 against 1.65 ms).
+template <int N>
+__device__ __forceinline__ void half_sum_n(double (&u)[N], double* buf) {
+  constexpr int H = N / 2;
+  half_rows_n(u);
+  const int lane = threadIdx.x & (kWave - 1);
+  if ((lane & 15) == 15) {
+#pragma unroll
+    for (int j = 0; j < H; ++j) buf[H * (lane >> 4) + j] = u[j];
+  }
+  wave_sync();
+  const double* mine = buf + N * (lane >> 5);
+#pragma unroll
+  for (int j = 0; j < N; ++j) u[j] = mine[j];
+}
+
+// The same for N FP32 values, the totals read from lanes 15, 31 (first half)
+// and 47, 63 (second half).
 template <int N>
 __device__ inline void half_sum_n(float (&u)[N]) {
   static_assert(N % 2 == 0, "N must be even");
