@@ -4,11 +4,12 @@
 // With r_i = (d_i - m_i) / sigma the adjoint of pixel i is
 //   dL/dm_i = -(2 / sigma) r_i dL/dchi2,
 // and dL/dp_k = sum_i dL/dm_i dm_i/dp_k.  Render, Jacobian and sums are FP64
-// (adjoint_sweep.hpp for Sersic stamps, sweep.hpp's FP64 instance for Moffat
-// stamps, each a kernel of its own so that neither holds the other's
-// registers): the FP32 rounding of the exponent b t is amplified where the
-// gradient components cancel over the stamp, up to ~1e-4 of the largest
-// component.  J^T J is summed only when it is asked for.
+// (adjoint_sweep.hpp for the Sersic stamps of large stamps and batches,
+// sweep.hpp's FP64 instance for the others and for Moffat stamps, each a kernel
+// of its own so that neither holds the other's registers): the FP32 rounding of
+// the exponent b t is amplified where the gradient components cancel over the
+// stamp, up to ~1e-4 of the largest component.  J^T J is summed only when it is
+// asked for.
 #include "kernels.hpp"
 #include "adjoint_sweep.hpp"
 
@@ -92,7 +93,7 @@ __device__ __forceinline__ void write_sums(const Acc<GRAD ? 0xFFu : 0u, double>&
 // with the gradient 3 (64 x 64 FP32 660 us; 4 spill more per stamp: 695, and 16 x
 // 16 314 -> 379; 2: 744), with J^T J 2, for chi^2 alone 5.
 template <int DT, bool GRAD, bool JTJ>
-__global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_sersic_kernel(
+__global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_tables_kernel(
     shape_batch b, const float* params, const float* grad_chi2, float* chi2, float* grad_p,
     float* jtj, float* jtr, int chunk) {
   __shared__ SersicTables tab;
@@ -132,9 +133,11 @@ __global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_sersic_ker
   }
 }
 
-// The Moffat stamps of a batch, one wave per stamp (sweep.hpp in FP64).
-template <int DT, bool GRAD, bool JTJ>
-__global__ __launch_bounds__(kWave, JTJ ? 2 : 5) void chi2_moffat_kernel(
+// The stamps of one model, one wave per stamp (sweep.hpp in FP64): Moffat
+// stamps, and the Sersic stamps of batches that do not earn the tables.  With
+// J^T J, FP16 stamps' rolled loops fit three waves per SIMD.
+template <int DT, int MODEL, bool GRAD, bool JTJ>
+__global__ __launch_bounds__(kWave, JTJ ? (DT == SHAPE_F32 ? 2 : 3) : 5) void chi2_kernel(
     shape_batch b, const float* params, const float* grad_chi2, float* chi2, float* grad_p,
     float* jtj, float* jtr) {
   constexpr uint32_t EM = GRAD ? 0xFFu : 0u;
@@ -143,34 +146,61 @@ __global__ __launch_bounds__(kWave, JTJ ? 2 : 5) void chi2_moffat_kernel(
   wave_sync();
   for (int64_t s = blockIdx.x; s < b.n; s += gridDim.x) {
     const Stamp st = stamp_info(b, s);
-    if (st.bad || st.model != SHAPE_MOFFAT) continue;  // the Sersic launch's
+    if (!st.bad && st.model != MODEL) continue;  // the other model's launch owns it
+    if (st.bad && MODEL != SHAPE_SERSIC) continue;
     double p[8];
-    if (!read_params(params, s, p)) {
+    if (!read_params(params, s, p) || st.bad) {
       if (lane == 0) write_nan<GRAD>(s, chi2, grad_p, jtj, jtr);
       continue;
     }
     Acc<EM, double> acc;
-    sweep<DT, SHAPE_MOFFAT, EM, kWave, double, kLayoutAny, JTJ>(
-        b, st, make_trial<double>(p, SHAPE_MOFFAT, p[5]), acc);
+    // a side that divides 64 takes the column-per-lane layout (the geometry
+    // as per-column quadratics), any other side the lane-stride walk
+    const Trial<double> tr = make_trial<double>(p, MODEL, p[5]);
+    if (rows_layout_fits(st.side))
+      sweep<DT, MODEL, EM, kWave, double, kLayoutRows, JTJ>(b, st, tr, acc);
+    else
+      sweep<DT, MODEL, EM, kWave, double, kLayoutAny, JTJ>(b, st, tr, acc);
     write_sums<GRAD, JTJ>(acc, st, s, grad_chi2, chi2, grad_p, jtj, jtr, lane);
   }
+}
+
+// Whether the Sersic stamps of a batch take the tables: from a mean area of 48 x
+// 48, or where the batch holds 3e7 pixels (but for the normal matrix of FP16
+// stamps, whose three waves per SIMD stay the faster there).  A stamp's own
+// tables and a workgroup's cost 600 instructions, which small stamps do not earn
+// back, nor batches too small to give a workgroup several stamps.  Time against
+// chi2_kernel's (chi^2, gradient, normal matrix): side 48 and up 0.5-0.99 at
+// every size; 12 to 37 above 3e7 pixels 0.80-1.02, 0.78-0.90, 0.85-0.99 (FP16
+// normal matrix 0.99-1.11); at 1.2e7 pixels 0.96-1.4, 0.86-1.11, 0.94-1.16; at
+// 3e6 1.1-2.1, 0.9-1.4, 1.05-1.44.
+template <int DT, bool JTJ>
+bool takes_tables(const shape_batch& b) {
+  const int64_t area = b.side ? b.n_pixels : b.n * ((int64_t)b.side0 * b.side0);
+  if (area >= b.n * (48 * 48)) return true;
+  return area >= 30000000 && !(JTJ && DT == SHAPE_F16_SCALED);
 }
 
 template <int DT, bool GRAD, bool JTJ>
 hipError_t launch_dt(const shape_batch& b, const float* params, const float* grad_chi2,
                      float* chi2, float* grad_p, float* jtj, float* jtr, hipStream_t stream) {
-  // chunks of up to kChi2Chunk stamps that still make 8,192 workgroups, a few
-  // rounds over the card
-  const int64_t most = b.n / 8192, chunk = most < 1 ? 1 : most > kChi2Chunk ? kChi2Chunk : most;
-  const int64_t groups = (b.n + chunk - 1) / chunk, cap = 1ll << 25;
-  hipLaunchKernelGGL((chi2_sersic_kernel<DT, GRAD, JTJ>),
-                     dim3((unsigned)(groups < cap ? groups : cap)), dim3(kWave), 0, stream, b,
-                     params, grad_chi2, chi2, grad_p, jtj, jtr, (int)chunk);
+  const dim3 g((unsigned)(b.n < (1ll << 30) ? b.n : (1ll << 30))), t(kWave);
+  if (takes_tables<DT, JTJ>(b)) {
+    // chunks of up to kChi2Chunk stamps that still make 8,192 workgroups, a few
+    // rounds over the card
+    const int64_t most = b.n / 8192, chunk = most < 1 ? 1 : most > kChi2Chunk ? kChi2Chunk : most;
+    const int64_t groups = (b.n + chunk - 1) / chunk, cap = 1ll << 25;
+    hipLaunchKernelGGL((chi2_tables_kernel<DT, GRAD, JTJ>),
+                       dim3((unsigned)(groups < cap ? groups : cap)), t, 0, stream, b, params,
+                       grad_chi2, chi2, grad_p, jtj, jtr, (int)chunk);
+  } else {
+    hipLaunchKernelGGL((chi2_kernel<DT, SHAPE_SERSIC, GRAD, JTJ>), g, t, 0, stream, b, params,
+                       grad_chi2, chi2, grad_p, jtj, jtr);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !b.model) return e;
-  const int64_t grid = b.n < (1ll << 30) ? b.n : (1ll << 30);
-  hipLaunchKernelGGL((chi2_moffat_kernel<DT, GRAD, JTJ>), dim3((unsigned)grid),
-                     dim3(kWave), 0, stream, b, params, grad_chi2, chi2, grad_p, jtj, jtr);
+  hipLaunchKernelGGL((chi2_kernel<DT, SHAPE_MOFFAT, GRAD, JTJ>), g, t, 0, stream, b, params,
+                     grad_chi2, chi2, grad_p, jtj, jtr);
   return hipGetLastError();
 }
 

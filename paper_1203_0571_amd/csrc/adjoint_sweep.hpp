@@ -24,9 +24,10 @@
 // exp2 tables, one wave per stamp (us; chi^2 / with gradient / with the normal
 // matrix): 65,536 of 64 x 64 FP32 628 / 809 / 1,170 -> 510 / 679 / 1,034, FP16
 // 623 / 796 / 1,112 -> 483 / 651 / 984; 20,000 of 48 x 48 FP16 129 / 184 / 256 ->
-// 99 / 135 / 223; 30,000 of 33 x 33 112 / 159 / 244 -> 100 / 138 / 238; 8,000 of
-// 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  40, 62 and 88 VALU instructions
-// per pixel and 500 to 1,000 per stamp; the SIMDs issue on about 90% of cycles.
+// 99 / 135 / 223; 8,000 of 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  Small
+// stamps in small batches keep that sweep (adjoint.hip).  40, 62 and 88 VALU
+// instructions per pixel and 500 to 1,000 per stamp; the SIMDs issue on about
+// 90% of cycles.
 #pragma once
 
 #include "sweep.hpp"

@@ -236,8 +236,8 @@ __device__ __forceinline__ Trial<T> make_trial(const double* p, int model, doubl
   const double I0 = p[6], twoinvD = 2.0 * iD;
   if (model == SHAPE_SERSIC) {
     const T n = (T)p[5], Re = (T)p[4];
-    // (FP64: by its series, once per stamp; the pixels' tables may not be filled)
-    const T invn = A::rcp(n), l2Re = kF32 ? A::lg2(Re) : (T)log2_series((double)Re);
+    // (FP64 for one lane's stamp: by its series, whoever uses it has no f64_tab)
+    const T invn = A::rcp(n), l2Re = kF32 || UNI ? A::lg2(Re) : (T)log2_series((double)Re);
     const double in = kF32 ? rcp_f64(p[5]) : 1.0 / p[5];
     const double iRe = kF32 ? rcp_f64(p[4]) : 1.0 / p[4];
     double b, db;
@@ -292,6 +292,13 @@ struct Px {
   T m0, h, c, t, q5, cR, r;
 };
 
+// The FP32 Sersic instance applies the constant factors k7 (of the x0, y0,
+// e1, e2 columns) and k4 (of the Re column) to the sums once, after the sweep.
+template <typename T, int MODEL>
+__host__ __device__ constexpr bool fold_factors() {
+  return sizeof(T) == 4 && MODEL == SHAPE_SERSIC;
+}
+
 // The residual of a pixel stored as `raw`.  FP16 storage in the FP32
 // instance: one rounding for the scale and the difference together.
 template <int DT, typename T>
@@ -304,10 +311,8 @@ __device__ __forceinline__ T residual(float raw, float scale, T m) {
     return (T)(raw * scale) - m;
 }
 
-// Renders a pixel stored as `raw` at R^2 = R2 (unfloored).  The Sersic columns'
-// constant factors k7 (of x0, y0, e1, e2) and k4 (of Re) are left out: they are
-// applied to the sums once, after the sweep.  FLOOR = false: the caller knows
-// that R2 is not below the model's floor (clear_of_floor).
+// Renders a pixel stored as `raw` at R^2 = R2 (unfloored).  FLOOR = false: the
+// caller knows that R2 is not below the model's floor (clear_of_floor).
 template <int DT, int MODEL, uint32_t EM, bool FLOOR, typename T>
 __device__ __forceinline__ Px<T> render(const Trial<T>& t, float raw, float scale, T R2) {
   using A = Arith<T>;
@@ -319,7 +324,10 @@ __device__ __forceinline__ Px<T> render(const Trial<T>& t, float raw, float scal
     p.t = A::ex2(A::fma(L, t.ha, t.hc));
     p.m0 = A::ex2(t.nb2 * p.t);
     p.c = p.m0 * p.t;
-    p.h = p.c * A::rcp(R2);
+    if constexpr (fold_factors<T, MODEL>())
+      p.h = p.c * A::rcp(R2);
+    else
+      p.h = p.c * A::rcp(R2) * t.k7;
     if constexpr (has(EM, 5)) p.q5 = A::fma(L, t.k5a, t.k5b);
   } else {
     const T base = A::fma(R2, t.irdsq, (T)1);
@@ -335,40 +343,53 @@ __device__ __forceinline__ Px<T> render(const Trial<T>& t, float raw, float scal
   return p;
 }
 
-// The moment form's constants of a sweep.  It takes R^2 in units of Re^2, s =
-// R^2 S with S = 1 / Re^2 (2^(hc / ha)): then t = 2^(ha log2 s) needs no added
-// constant, and t / R^2 = S 2^((ha - 1) log2 s) gives h without a reciprocal
-// (one transcendental fewer per pixel; S goes into the folded factor of the x0,
-// y0, e1, e2 columns, log2 S into the n column's constant).
+// The moment form's constants of a sweep.  The FP32 instance takes R^2 in
+// units of Re^2, s = R^2 S with S = 1 / Re^2 (2^(hc / ha)): then
+// t = 2^(ha log2 s) needs no added constant, and t / R^2 = S 2^((ha - 1) log2
+// s) gives h without a reciprocal (one transcendental fewer per pixel; S goes
+// into the folded factor of the x0, y0, e1, e2 columns, log2 S into the n
+// column's constant).
+template <typename T>
 struct MomentUnits {
-  float S = 1.0f, floor = Arith<float>::kR2Floor, ham1 = 0.0f, k5b = 0.0f;
+  T S = (T)1, floor = Arith<T>::kR2Floor, ham1 = (T)0, k5b = (T)0;
   __device__ __forceinline__ MomentUnits() {}
-  __device__ __forceinline__ explicit MomentUnits(const Trial<float>& t) {
-    using A = Arith<float>;
-    const float lS = A::uni(t.hc * A::rcp(t.ha));
-    S = A::uni(A::ex2(lS));
-    floor = A::uni(A::kR2Floor * S);
-    ham1 = A::uni(t.ha - 1.0f);
-    k5b = A::uni(A::fma(-lS, t.k5a, t.k5b));
+  __device__ __forceinline__ explicit MomentUnits(const Trial<T>& t) {
+    if constexpr (sizeof(T) == 4) {
+      using A = Arith<T>;
+      const T lS = A::uni(t.hc * A::rcp(t.ha));
+      S = A::uni(A::ex2(lS));
+      floor = A::uni(A::kR2Floor * S);
+      ham1 = A::uni(t.ha - (T)1);
+      k5b = A::uni(A::fma(-lS, t.k5a, t.k5b));
+    }
   }
 };
 
-// Renders a Sersic pixel stored as `raw` at s = R^2 S.
-template <int DT, uint32_t EM, bool FLOOR>
-__device__ __forceinline__ Px<float> render_moment(const Trial<float>& t, const MomentUnits& mu,
-                                                   float raw, float scale, float s2) {
-  using A = Arith<float>;
-  Px<float> p;
+// Renders a Sersic pixel stored as `raw` at s = R^2 S.  The FP64 instance (the
+// adjoint's; its exp2 costs more than its reciprocal) renders as render()
+// does, with the factors k7 and k4 in the columns.
+template <int DT, uint32_t EM, bool FLOOR, typename T>
+__device__ __forceinline__ Px<T> render_moment(const Trial<T>& t, const MomentUnits<T>& mu,
+                                               float raw, float scale, T s2) {
+  using A = Arith<T>;
+  Px<T> p;
   const bool floored = FLOOR && s2 < mu.floor;
   s2 = floored ? mu.floor : s2;
-  const float L = A::lg2(s2);
-  const float tr = A::ex2(L * mu.ham1);   // t / s
-  p.t = tr * s2;
-  p.m0 = A::ex2(t.nb2 * p.t);
-  p.c = p.m0 * p.t;
-  p.h = p.m0 * tr;                        // h / S
-  p.h = floored ? 0.0f : p.h;
-  if constexpr (has(EM, 5)) p.q5 = A::fma(L, t.k5a, mu.k5b);
+  const T L = A::lg2(s2);
+  if constexpr (sizeof(T) == 4) {
+    const T tr = A::ex2(L * mu.ham1);   // t / s
+    p.t = tr * s2;
+    p.m0 = A::ex2(t.nb2 * p.t);
+    p.c = p.m0 * p.t;
+    p.h = p.m0 * tr;                    // h / S
+  } else {
+    p.t = A::ex2(A::fma(L, t.ha, t.hc));
+    p.m0 = A::ex2(t.nb2 * p.t);
+    p.c = p.m0 * p.t;
+    p.h = p.c * A::rcp(s2) * t.k7;
+  }
+  p.h = floored ? (T)0 : p.h;
+  if constexpr (has(EM, 5)) p.q5 = A::fma(L, t.k5a, sizeof(T) == 4 ? mu.k5b : t.k5b);
   p.r = residual<DT>(raw, scale, A::fma(t.I0, p.m0, t.sky));
   return p;
 }
@@ -416,21 +437,24 @@ struct Walk {
 
 // A lane's moment sums (see sweep's kMom): M_s = sum h^2 u2^s, X_vj = sum H_j
 // J_v for the Re, n and I0 columns, Y_j = sum H_j, g_j = sum H_j r.
+template <typename T>
 struct Moments {
-  float M[5] = {}, X[3][3] = {}, Y[3] = {};
+  T M[5] = {}, X[3][3] = {}, Y[3] = {};
   double g[3] = {};
 };
 
 // The column sums from a lane's moments, in FP64: column k is
 // h sum_j C[k][j] u2^j (degree 1 for x0, y0, 2 for e1, e2).  Forms J^T r
 // (GR), the sky column's sums (GY), those against Re, n and I0 (GX) and the
-// four columns' own (GM).  The factor k7 S of these columns (and k4 of the Re
-// column) is folded in here, not into the sums afterwards.
-template <uint32_t EM, bool JTJ, bool GR, bool GY, bool GX, bool GM>
-__device__ __forceinline__ void recombine(const Trial<float>& t, const MomentUnits& mu,
-                                          const Column<float>& col, const Moments& m,
-                                          Acc<EM, float>& acc) {
-  const double f7 = (double)(t.k7 * mu.S), f4 = (double)t.k4;
+// four columns' own (GM).  The FP32 instance folds the factor k7 S of these
+// columns (and k4 of the Re column) in here, not into the sums afterwards.
+template <uint32_t EM, bool JTJ, bool GR, bool GY, bool GX, bool GM, typename T>
+__device__ __forceinline__ void recombine(const Trial<T>& t, const MomentUnits<T>& mu,
+                                          const Column<T>& col, const Moments<T>& m,
+                                          Acc<EM, T>& acc) {
+  constexpr bool kF32 = sizeof(T) == 4;
+  const double f7 = kF32 ? (double)(t.k7 * mu.S) : 1.0;
+  const double f4 = kF32 ? (double)t.k4 : 1.0;
   const double C[4][3] = {{col.c3 * f7, t.n12 * f7, 0.0},
                           {col.c4 * f7, t.n22 * f7, 0.0},
                           {col.p2c * f7, col.p2b * f7, t.p2a * f7},
@@ -457,10 +481,10 @@ __device__ __forceinline__ void recombine(const Trial<float>& t, const MomentUni
     }
     if constexpr (GR) acc.g[a] = g;
     if constexpr (JTJ) {
-      if (GY && has(EM, 7)) acc.A[tri(a, 7)] = (float)y;
+      if (GY && has(EM, 7)) acc.A[tri(a, 7)] = (T)y;
 #pragma unroll
       for (int v = 0; v < 3; ++v)
-        if (GX && has(EM, 4 + v)) acc.A[tri(a, 4 + v)] = (float)x[v];
+        if (GX && has(EM, 4 + v)) acc.A[tri(a, 4 + v)] = (T)x[v];
     }
   }
   // P[c][i] = sum_j C[c][j] M[i + j]; entry (a, c) = sum_i C[a][i] P[c][i]
@@ -485,7 +509,7 @@ __device__ __forceinline__ void recombine(const Trial<float>& t, const MomentUni
         double q = 0.0;
 #pragma unroll
         for (int i = 0; i < da; ++i) q = fma(C[a][i], P[c2][i], q);
-        acc.A[tri(a, c2)] = (float)q;
+        acc.A[tri(a, c2)] = (T)q;
       }
     }
   }
@@ -604,18 +628,19 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
   T c2p = (T)0, gp[8];
 #pragma unroll
   for (int k = 0; k < 8; ++k) gp[k] = (T)0;
-  // Moment form of the row layout (Sersic with x0, y0, e1, e2 free): along a
-  // lane's column the four shape columns are h times polynomials in u2 of
-  // degree 1, 1, 2, 2 with per-column coefficients, J_k = sum_j C_kj h u2^j.
-  // The lane therefore sums H_j = h u2^j (j = 0..2) against the other
-  // quantities instead of the four columns: M_s = sum h^2 u2^s (s = 0..4) for
-  // the 4 x 4 block, sum H_j v for v = J_Re, J_n, J_I0, 1 and r, and forms the
-  // column sums from them once per sweep -- 22 VALU operations per pixel where
-  // the columns cost 40.
-  constexpr bool kMom = MODEL == SHAPE_SERSIC && LAYOUT == kLayoutRows && (EM & 0xFu) == 0xFu;
-  static_assert(MODEL == SHAPE_MOFFAT || sizeof(T) == 4, "FP64 Sersic: adjoint_sweep.hpp");
-  static_assert(LAYOUT == kLayoutAny || (sizeof(T) == 4 && JTJ), "the fit's layouts");
-  Moments mom;
+  constexpr bool kFold = fold_factors<T, MODEL>();
+  // Moment form of the row layout (Sersic with x0, y0, e1, e2 free; the FP32
+  // instance of the fit and the FP64 instance of the adjoint):
+  // along a lane's column the four shape columns are h times polynomials in
+  // u2 of degree 1, 1, 2, 2 with per-column coefficients, J_k = sum_j C_kj
+  // h u2^j.  The lane therefore sums H_j = h u2^j (j = 0..2) against the
+  // other quantities instead of the four columns: M_s = sum h^2 u2^s
+  // (s = 0..4) for the 4 x 4 block, sum H_j v for v = J_Re, J_n, J_I0, 1 and
+  // r, and forms the column sums from them once per sweep -- 22 VALU
+  // operations per pixel where the columns cost 40.
+  constexpr bool kMom = MODEL == SHAPE_SERSIC && LAYOUT == kLayoutRows && (EM & 0xFu) == 0xFu &&
+                        (sizeof(T) == 8 || JTJ);
+  Moments<T> mom;
   T gq[3] = {(T)0, (T)0, (T)0};
   auto flush = [&]() {
     if constexpr (kFlush > 0 && kGrad) {
@@ -650,7 +675,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     const T m0 = px.m0, h = px.h, r = px.r;
     T J[8];
     if constexpr (MODEL == SHAPE_SERSIC) {
-      if constexpr (has(EM, 4)) J[4] = px.c;
+      if constexpr (has(EM, 4)) J[4] = kFold ? px.c : px.c * t.k4;
       if constexpr (has(EM, 5)) J[5] = px.c * px.q5;
     } else {
       if constexpr (has(EM, 4)) J[4] = px.cR * t.k4;
@@ -668,8 +693,9 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     J[7] = (T)1;
     // J[a] = px_x[a] px_y[a] (x 1: m0 is no product)
     constexpr bool kSersic = MODEL == SHAPE_SERSIC;
-    const T px_x[7] = {h, h, h, h, kSersic ? m0 : px.cR, kSersic ? px.c : m0 * px.q5, m0};
-    const T px_y[7] = {n1, n2, P2, P3, kSersic ? px.t : t.k4, kSersic ? px.q5 : t.k5a, (T)1};
+    const T px_x[7] = {h, h, h, h, kSersic ? (kFold ? m0 : px.c) : px.cR,
+                       kSersic ? px.c : m0 * px.q5, m0};
+    const T px_y[7] = {n1, n2, P2, P3, kFold ? px.t : t.k4, kSersic ? px.q5 : t.k5a, (T)1};
     const double rd = (double)r;
     if constexpr (kFlush > 0)
       c2p = first ? r * r : A::fma(r, r, c2p);
@@ -698,57 +724,73 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
   };
   // The moment form's pixel (kMom): the H_j sums; the Re, n, I0 and sky columns
   // are summed among themselves as in pixel().
-  const MomentUnits mu = [&] {
+  constexpr bool kF32Mom = kMom && sizeof(T) == 4;
+  const MomentUnits<T> mu = [&] {
     if constexpr (kMom)
-      return MomentUnits(t);
+      return MomentUnits<T>(t);
     else
-      return MomentUnits();
+      return MomentUnits<T>();
   }();
-  auto mom_pixel = [&](auto fused, auto flr, const auto& t, const float d, const float u2,
-                       const float s2, const bool first) {
+  auto mom_pixel = [&](auto fused, auto flr, const float d, const T u2, const T s2,
+                       const bool first) {
     constexpr bool kFused = decltype(fused)::value;
-    const Px<float> px = render_moment<DT, EM, decltype(flr)::value>(t, mu, d, st.scale, s2);
-    const float m0 = px.m0, c = px.c, h = px.h, r = px.r;
-    float J[8];
-    J[4] = c;
+    const Px<T> px = render_moment<DT, EM, decltype(flr)::value>(t, mu, d, st.scale, s2);
+    const T m0 = px.m0, c = px.c, h = px.h, r = px.r;
+    T J[8];
+    J[4] = kF32Mom ? c : c * t.k4;
     if constexpr (has(EM, 5)) J[5] = c * px.q5;
     J[6] = m0;
-    J[7] = 1.0f;
-    float H[3];
+    J[7] = (T)1;
+    T H[3];
     H[0] = h;
 #pragma unroll
     for (int j = 1; j < 3; ++j) H[j] = H[j - 1] * u2;
-    c2p = first ? r * r : A::fma(r, r, c2p);
+    if constexpr (kFlush > 0) {
+      c2p = first ? r * r : A::fma(r, r, c2p);
 #pragma unroll
-    for (int j = 0; j < 3; ++j) gq[j] = first ? H[j] * r : A::fma(H[j], r, gq[j]);
+      for (int j = 0; j < 3; ++j) gq[j] = first ? H[j] * r : A::fma(H[j], r, gq[j]);
+    } else {
+      acc.c2 = fma((double)r, (double)r, acc.c2);
 #pragma unroll
-    for (int s = 0; s < 5; ++s) {
-      if (!(SUMS & kSumsShape)) continue;
-      const int i = s < 3 ? s : 2, j = s - i;   // H_i H_j, i + j = s
-      mom.M[s] = A::fma(H[i], H[j], mom.M[s]);
+      for (int j = 0; j < 3; ++j) mom.g[j] = fma((double)H[j], (double)r, mom.g[j]);
+    }
+    if constexpr (JTJ) {
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        if (!(SUMS & kSumsShape)) continue;
+        const int i = s < 3 ? s : 2, j = s - i;   // H_i H_j, i + j = s
+        mom.M[s] = A::fma(H[i], H[j], mom.M[s]);
+      }
     }
 #pragma unroll
     for (int a = 4; a < 8; ++a) {
       if (!has(EM, a)) continue;
-      gp[a] = (a == 7) ? (first ? r : gp[a] + r) : (first ? J[a] * r : A::fma(J[a], r, gp[a]));
+      if constexpr (kFlush > 0)
+        gp[a] = (a == 7) ? (first ? r : gp[a] + r) : (first ? J[a] * r : A::fma(J[a], r, gp[a]));
+      else
+        acc.g[a] = (a == 7) ? acc.g[a] + (double)r : fma((double)J[a], (double)r, acc.g[a]);
+      if constexpr (JTJ) {
 #pragma unroll
-      for (int j = 0; j < 3; ++j)
-        if (!(SUMS & (a == 7 ? kSumsProfile : kSumsCross)))
-          continue;
-        else if (a == 7)
-          mom.Y[j] = j == 0 ? add_product<false>(h, 1.0f, h, mom.Y[0])
-                            : add_product<kFused>(H[j > 0 ? j - 1 : 0], u2, H[j], mom.Y[j]);
-        else
-          mom.X[a - 4][j] = A::fma(H[j], J[a], mom.X[a - 4][j]);
+        for (int j = 0; j < 3; ++j)
+          if (!(SUMS & (a == 7 ? kSumsProfile : kSumsCross)))
+            continue;
+          else if (a == 7)
+            mom.Y[j] = j == 0 ? add_product<false>(h, (T)1, h, mom.Y[0])
+                              : add_product<kFused>(H[j > 0 ? j - 1 : 0], u2, H[j], mom.Y[j]);
+          else
+            mom.X[a - 4][j] = A::fma(H[j], J[a], mom.X[a - 4][j]);
 #pragma unroll
-      for (int c2 = a; c2 < 8; ++c2) {
-        if (!has(EM, c2) || (c2 == 7 && a == 7) || !in_sums(SUMS, a, c2)) continue;
-        if (c2 == 7)
-          acc.A[tri(a, c2)] = a == 4   ? add_product<kFused>(m0, px.t, J[4], acc.A[tri(a, c2)])
-                              : a == 5 ? add_product<kFused>(c, px.q5, J[5], acc.A[tri(a, c2)])
-                                       : acc.A[tri(a, c2)] + m0;
-        else
-          acc.A[tri(a, c2)] = A::fma(J[a], J[c2], acc.A[tri(a, c2)]);
+        for (int c2 = a; c2 < 8; ++c2) {
+          if (!has(EM, c2) || (c2 == 7 && a == 7) || !in_sums(SUMS, a, c2)) continue;
+          if (c2 == 7)
+            acc.A[tri(a, c2)] =
+                a == 4   ? add_product<kFused>(kF32Mom ? m0 : c, kF32Mom ? px.t : t.k4, J[4],
+                                               acc.A[tri(a, c2)])
+                : a == 5 ? add_product<kFused>(c, px.q5, J[5], acc.A[tri(a, c2)])
+                         : acc.A[tri(a, c2)] + m0;
+          else
+            acc.A[tri(a, c2)] = A::fma(J[a], J[c2], acc.A[tri(a, c2)]);
+        }
       }
     }
   };
@@ -776,24 +818,27 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     const int nstep = st.npix / kWave;
     const void* sp = stamp_base<DT>(b, st);
     // FP32 stamps in memory, whole runs of kRun rows (sides 32 and 64): the
-    // run is unrolled, so its loads issue together and its first pixel opens
-    // the partials (2 fewer VALU per pixel); measured on 262,144 64 x 64
-    // stamps: fit 23.1 -> 20.8 ms, 32 x 32 4-parameter fit 3.72 -> 2.83 ms.
-    // FP16 stamps staged in LDS ran 5% slower unrolled (4% in the moment form:
-    // 18.1 vs 17.5 ms) and keep the loop.
+    // run is unrolled, so its loads issue together, and in the FP32 instance
+    // its first pixel opens the partials (2 fewer VALU per pixel); measured
+    // on 262,144 64 x 64 stamps: fit 23.1 -> 20.8 ms, 32 x 32 4-parameter fit
+    // 3.72 -> 2.83 ms; FP64 chi^2 0.74 -> 0.72 ms, with J^T J 1.47 -> 1.33 ms
+    // (65,536 stamps).  FP16 stamps staged in LDS ran 5% slower unrolled (4%
+    // in the moment form: 18.1 vs 17.5 ms) and keep the loop, as does the
+    // FP64 gradient without J^T J, whose five waves per SIMD leave the
+    // unrolled run too few registers (136 spilled, 4x slower).
     constexpr int kRun = 8;
     static_assert(kFlush == 0 || kFlush == kRun, "a run is one partial-sum block");
     // The sweeps of part of the sums (SUMS), one wave per SIMD with registers to
     // spare, are unrolled in either storage.
     constexpr bool kPart = SUMS != kSumsAll;
-    constexpr bool kUnroll = kPart || DT == SHAPE_F32;
+    constexpr bool kUnroll = kPart || (DT == SHAPE_F32 && (sizeof(T) == 4 || EM == 0u || JTJ));
     using RunFused = std::bool_constant<kMom || DT == SHAPE_F32>;   // sums_fused of whole runs
     const bool blocked = kUnroll && nstep % kRun == 0;   // wave-uniform
     // R^2 S along the column (the moment form's units)
     const T qas = A::uni(t.qa * mu.S), qbs = col.qb * mu.S, qcs = col.qc * mu.S;
     auto row_pixel = [&](auto fused, auto flr, const float d, const T u2, const bool first) {
       if constexpr (kMom)
-        mom_pixel(fused, flr, t, d, u2, A::fma(A::fma(qas, u2, qbs), u2, qcs), first);
+        mom_pixel(fused, flr, d, u2, A::fma(A::fma(qas, u2, qbs), u2, qcs), first);
       else
         pixel(fused, flr, d, col.R2(t, u2), col.n1(t, u2), col.n2(t, u2), col.P2(t, u2),
               col.P3(t, u2), first);
@@ -1025,7 +1070,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     }
   }
   flush();
-  if constexpr (MODEL == SHAPE_SERSIC) {
+  if constexpr (kFold) {
     // the folded constant factors: column a of J is s_a times what was summed
     // (the moment form folded them into its recombination, but for the
     // Re column's sums among the Re, n, I0 and sky columns)

@@ -43,21 +43,29 @@ def _stamps(side, storage, n=16):
     return p, pix, rng.uniform(1.0, 3.0, n).astype(np.float32)
 
 
+@pytest.mark.parametrize("large", [False, True])
 @pytest.mark.parametrize("storage", ["f32", "f16"])
 @pytest.mark.parametrize("side", [4, 5, 8, 16, 31, 33, 48, 63, 64, 65, 100, 128])
-def test_sersic_sweep_vs_oracle(shape, side, storage):
+def test_sersic_sweep_vs_oracle(shape, side, storage, large):
     """Outputs are FP64 sums (series good to 5e-14) rounded to FP32 (6e-8): 1e-6
-    of each, and of entries down to 1e-3 of the largest where terms cancel."""
+    of each, and of entries down to 1e-3 of the largest where terms cancel.
+    large: a batch of 3e7 pixels, which takes the tables at every side."""
     import torch
     p, pix, sigma = _stamps(side, storage)
     n = len(p)
-    scale = torch.full((n,), 0.5, device="cuda") if storage == "f16" else None
-    db = shape.DeviceBatch(pixels=torch.from_numpy(pix).cuda().reshape(-1),
-                           sigma=torch.from_numpy(sigma).cuda(), side0=side, scale=scale)
-    pt = torch.from_numpy(p.astype(np.float32)).cuda()
-    value = shape.chi2_fwd(db, pt).cpu().numpy()
-    plain = {k: v.cpu().numpy() for k, v in shape.chi2_bwd(db, pt).items() if v is not None}
-    full = {k: v.cpu().numpy() for k, v in shape.chi2_bwd(db, pt, want_normal=True).items()}
+    k = 30_000_000 // (n * side * side) + 1 if large else 1
+    db = shape.DeviceBatch(pixels=torch.from_numpy(pix).cuda().reshape(-1).repeat(k),
+                           sigma=torch.from_numpy(sigma).cuda().repeat(k), side0=side,
+                           scale=torch.full((n * k,), 0.5, device="cuda") if storage == "f16" else None)
+    pt = torch.from_numpy(p.astype(np.float32)).cuda().repeat(k, 1)
+
+    def first(t):   # every copy of the stamps gives the same bits
+        a = t.reshape((k, n) + t.shape[1:])
+        assert bool(((a == a[:1]) | ((a != a) & (a[:1] != a[:1]))).all())
+        return a[0].cpu().numpy()
+    value = first(shape.chi2_fwd(db, pt))
+    plain = {q: first(v) for q, v in shape.chi2_bwd(db, pt).items() if v is not None}
+    full = {q: first(v) for q, v in shape.chi2_bwd(db, pt, want_normal=True).items()}
     img = pix.astype(np.float64) * (0.5 if storage == "f16" else 1.0)
     for out in (value, plain["chi2"], plain["grad"], full["grad"], full["jtj"]):
         assert np.isnan(out[14]).all()
@@ -78,18 +86,19 @@ def test_sersic_sweep_vs_oracle(shape, side, storage):
 
 
 def test_chunks_of_stamps_do_not_change_the_results(shape):
-    """A workgroup takes up to 8 stamps of a large batch and one of a small one."""
+    """A workgroup takes several stamps of a large batch and one of a small one,
+    skipping the other model's."""
     import torch
-    p, pix, sigma = _stamps(5, "f32")
+    p, pix, sigma = _stamps(48, "f32")
     model = np.zeros(len(p), np.uint8)
     model[3::4] = 1
     p[3::4, 5] = 3.0
     out = []
-    for k in (1, 4097):     # 16 and 65,552 stamps
+    for k in (1, 1025):     # 16 and 16,400 stamps
         t = lambda x: torch.from_numpy(np.tile(x, (k,) + (1,) * (x.ndim - 1))).cuda()   # noqa: E731
-        db = shape.DeviceBatch(pixels=t(pix).reshape(-1), sigma=t(sigma), side0=5, model=t(model))
+        db = shape.DeviceBatch(pixels=t(pix).reshape(-1), sigma=t(sigma), side0=48, model=t(model))
         out.append(shape.chi2_bwd(db, t(p.astype(np.float32)), want_normal=True))
     for key in ("chi2", "grad", "jtj"):
         small, large = (o[key].cpu().numpy() for o in out)
-        np.testing.assert_array_equal(large.reshape((4097,) + small.shape),
-                                      np.broadcast_to(small, (4097,) + small.shape))
+        np.testing.assert_array_equal(large.reshape((1025,) + small.shape),
+                                      np.broadcast_to(small, (1025,) + small.shape))
