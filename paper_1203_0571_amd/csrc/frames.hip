@@ -324,16 +324,19 @@ constexpr int kScanDepth = 4;
 template <int DT>
 constexpr int kScanVec = DT == SHAPE_F32 ? 4 : 8;
 
+// kScanVec pixels from any pixel on: the types ask for no more than the pixel's
+// own alignment, and the vector is one load all the same.  FP32 frames of odd
+// pixel counts lose nothing by it; FP16 vectors on odd addresses read slower
+// (4,000 frames of 517 x 333 261 -> 311 us).
 template <int DT>
 __device__ __forceinline__ void load_vec(const void* p, float scale, float (&v)[kScanVec<DT>]) {
   if constexpr (DT == SHAPE_F32) {
-    const float4 q = *static_cast<const float4*>(p);
-    v[0] = q.x;
-    v[1] = q.y;
-    v[2] = q.z;
-    v[3] = q.w;
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    const f4 q = *static_cast<const f4*>(p);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] = q[c];
   } else {
-    typedef _Float16 h8 __attribute__((ext_vector_type(8)));
+    typedef _Float16 h8 __attribute__((ext_vector_type(8), aligned(2)));
     const h8 q = *static_cast<const h8*>(p);
 #pragma unroll
     for (int c = 0; c < 8; ++c) v[c] = (float)q[c] * scale;
@@ -349,10 +352,10 @@ __device__ __forceinline__ void load_vec(const void* p, float scale, float (&v)[
 // Of the brightest pixel a thread remembers only which of its batches first
 // held it; the threads that hold the chunk's maximum look their batch up
 // again.  The border is summed from the chunk's own rows, just read.
-// Measured: 4,096 frames of 512 x 512 in 726 us (5.9 TB/s; a 4 GiB device
-// copy reaches 4.6) and 35 us for place_kernel, 792 us for detect_kernel; 4
-// frames of 2048 x 2048 in 16 us and 8 us, 783 us for detect_kernel, whose
-// four workgroups read 86 GB/s.
+// Measured with place_kernel: 4,096 frames of 512 x 512 FP32 in 732 us (5.9
+// TB/s; a 4 GiB device copy reaches 4.6), 797 us for detect_kernel; 4 frames of
+// 2048 x 2048 in 22 us, 776 us for detect_kernel, whose four workgroups read 86
+// GB/s.
 template <int DT>
 __global__ __launch_bounds__(kFrameThreads) void scan_kernel(shape_frames f, int64_t chunk,
                                                              int64_t chunks, FramePart* parts) {
@@ -370,10 +373,9 @@ __global__ __launch_bounds__(kFrameThreads) void scan_kernel(shape_frames f, int
     const int e = (int)(a + chunk < npix ? a + chunk : npix);
     const float scale = (DT == SHAPE_F16_SCALED) ? f.scale[fr] : 1.0f;
     const E* fp = static_cast<const E*>(f.pixels) + fr * npix;
-    // [a, va) and [vb, e) pixel by pixel, [va, vb) in aligned vectors
-    const int mis = (int)(reinterpret_cast<uintptr_t>(fp + a) % 16 / sizeof(E));
-    const int va = min(a + (mis ? V - mis : 0), e);
-    const int nv = (e - va) / V, vb = va + nv * V;
+    // [a, vb) in vectors, wherever the frame lies in memory (its sums must not
+    // depend on that), [vb, e) pixel by pixel
+    const int nv = (e - a) / V, vb = a + nv * V;
     double sum[2] = {0.0, 0.0};
     float vmax = -__builtin_inff(), vmin = __builtin_inff();
     int at = -1;   // the batch of the maximum: its first vector, or -1: a single pixel
@@ -387,7 +389,6 @@ __global__ __launch_bounds__(kFrameThreads) void scan_kernel(shape_frames f, int
         k1 = k;
       }
     };
-    if (tid < va - a) single(a + tid);
     if (tid < e - vb) single(vb + tid);
     constexpr int kStep = kFrameThreads * kScanDepth;
     float bmax = -__builtin_inff();
@@ -397,7 +398,7 @@ __global__ __launch_bounds__(kFrameThreads) void scan_kernel(shape_frames f, int
       for (int u = 0; u < kScanDepth; ++u) {
         // past the end: the batch's first vector again, left out of the sum
         const int qu = q + u * kFrameThreads;
-        load_vec<DT>(fp + va + (int64_t)(qu < nv ? qu : q) * V, scale, v[u]);
+        load_vec<DT>(fp + a + (int64_t)(qu < nv ? qu : q) * V, scale, v[u]);
       }
       float m = v[0][0];
 #pragma unroll
@@ -466,10 +467,10 @@ __global__ __launch_bounds__(kFrameThreads) void scan_kernel(shape_frames f, int
         const int qu = at + u * kFrameThreads;
         if (qu >= nv) continue;
         float v[V];
-        load_vec<DT>(fp + va + (int64_t)qu * V, scale, v);
+        load_vec<DT>(fp + a + (int64_t)qu * V, scale, v);
 #pragma unroll
         for (int c = V - 1; c >= 0; --c)
-          if (v[c] == cmax) k0 = min(k0, va + qu * V + c);
+          if (v[c] == cmax) k0 = min(k0, a + qu * V + c);
       }
     }
     if (k0 < npix) atomicMin(&first, k0);
@@ -551,17 +552,20 @@ __global__ __launch_bounds__(kFrameThreads) void place_kernel(shape_frames f, in
   }
 }
 
-// Pixels a workgroup of scan_kernel reads: one batch of vectors per thread at
-// least, so that a single frame spreads over the card; with many pixels in
-// all, up to kMaxChunk, where the records and the workgroup's end stop
-// counting.
-constexpr int64_t kMaxChunk = 65536;
+// Pixels a workgroup of scan_kernel reads: a frame is cut by its own size alone,
+// so that its sums round alike however many frames it is measured with.  At
+// most two batches of vectors per thread in FP32, four in FP16 (32 and 64 KiB),
+// whole batches, about equal parts.  One batch costs large calls the workgroup's
+// end, longer chunks cost a single frame its spread (us at 1 / 2 / 4 / 8 batches):
+// 4,096 frames of 512 x 512 FP32 843 / 732 / 728 / 734, FP16 550 / 418 / 390 / 405; 4
+// of 2048 x 2048 FP32 24 / 22 / 22 / 22, FP16 18 / 16 / 16 / 17; one of 512 x 512 FP32
+// 11.3 / 10.9 / 12.5 / 13.6.
 int64_t scan_chunk(const shape_frames& f) {
   const int64_t npix = (int64_t)f.height * f.width;
   const int64_t batch = (int64_t)kFrameThreads * kScanDepth * (f.dtype == SHAPE_F32 ? 4 : 8);
-  const int64_t spread = f.n * npix / 4096;
-  int64_t chunk = spread < batch ? batch : spread > kMaxChunk ? kMaxChunk : spread;
-  chunk = (chunk + batch - 1) / batch * batch;
+  const int64_t most = (f.dtype == SHAPE_F32 ? 2 : 4) * batch;
+  const int64_t parts = (npix + most - 1) / most;
+  const int64_t chunk = ((npix + parts - 1) / parts + batch - 1) / batch * batch;
   return chunk < npix ? chunk : npix;
 }
 
