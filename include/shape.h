@@ -412,9 +412,13 @@ int shape_frame_detect(const shape_frames* frames, int32_t max_side, float* info
  * between calls.
  *   shape_frame_workspace_bytes: the bytes ws needs for these frames (a
  *   function of n, height, width and dtype).
+ * Frames of at most SHAPE_FRAME_WHOLE pixels are read by one workgroup each all
+ * the same, faster for them: for these the call is shape_frame_detect, and ws
+ * is checked but not used.
  * Errors: as shape_frame_detect; SHAPE_EINVAL for a NULL or misaligned ws,
  * SHAPE_ENOMEM for too few bytes.
  */
+#define SHAPE_FRAME_WHOLE 36864
 int shape_frame_workspace_bytes(const shape_frames* frames, size_t* bytes);
 int shape_frame_detect_ws(const shape_frames* frames, int32_t max_side, float* info,
                           int32_t* peak, int32_t* box, uint32_t* status, void* ws,

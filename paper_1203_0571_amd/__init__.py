@@ -44,6 +44,7 @@ REC_LEN = 9
 MASK_ALL = 0xFF
 MASK_SIZE = 0xF0
 STATIC_MAX_STAMPS = 65536   # SHAPE_STATIC_MAX_STAMPS: shape_fit_queue_static's limit
+FRAME_WHOLE = 36864         # SHAPE_FRAME_WHOLE: frames up to here need no scratch memory
 
 
 class ShapeBatch(C.Structure):
@@ -449,11 +450,16 @@ def sersic_chi2(params: torch.Tensor, batch: DeviceBatch) -> torch.Tensor:
 
 
 def frame_detect(frames: DeviceFrames, max_side: int = 128):
-    """shape_frame_detect_ws: dict(info [n,3] = sky, r50, F; peak [n,2]; box [n,3]; status)."""
+    """shape_frame_detect_ws, or shape_frame_detect for frames of at most FRAME_WHOLE
+    pixels: dict(info [n,3] = sky, r50, F; peak [n,2]; box [n,3]; status)."""
     n, dev = frames.n, frames.device
     info, peak, box, st = _outs(n, dev, ((n, 3), torch.float32), ((n, 2), torch.int32),
                                 ((n, 3), torch.int32), ((n,), torch.int32))
     f = frames.c_struct()
+    if f.height * f.width <= FRAME_WHOLE:
+        _check(lib.shape_frame_detect(C.byref(f), int(max_side), _ptr(info), _ptr(peak), _ptr(box),
+                                      _ptr(st), _stream(dev)), "shape_frame_detect")
+        return dict(info=info, peak=peak, box=box, status=st)
     nb = C.c_size_t()
     _check(lib.shape_frame_workspace_bytes(C.byref(f), C.byref(nb)), "shape_frame_workspace_bytes")
     ws = torch.empty(nb.value, dtype=torch.uint8, device=dev)

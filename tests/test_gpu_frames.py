@@ -204,3 +204,33 @@ def test_split_frames_match_one_workgroup_per_frame(shape, H, W, f16):
     assert (np.isfinite(g["info"][:, 2]) == ok).all()
     tol = 2.0 ** -22 * np.abs(ref["info"][:, 2]) + 2.0 ** -50 * H * W * top
     assert (np.abs(g["info"][:, 2] - ref["info"][:, 2])[ok] <= tol[ok]).all()
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("H,W", [(4, 4), (64, 64), (91, 93), (192, 192)])
+def test_small_frames_are_read_by_one_workgroup_each(shape, H, W, f16):
+    """Frames of up to SHAPE_FRAME_WHOLE pixels give shape_frame_detect's results
+    bit for bit, with and without scratch memory; pixels whose sum cancels, so
+    that another order of summation would show in F."""
+    import ctypes as C
+
+    import torch
+    rng = np.random.default_rng(H * W)
+    n, half = 40, H * W // 2
+    a = np.exp2(rng.uniform(-24, 15, (n, half)) if f16 else rng.uniform(-20, 20, (n, half)))
+    v = np.concatenate([a, -a, np.zeros((n, H * W - 2 * half))], 1)
+    v = rng.permuted(v, axis=1).reshape(n, H, W).astype(np.float16 if f16 else np.float32)
+    fr, g = _gpu_detect(shape, v, scale=np.full(n, 0.3, np.float32) if f16 else None)
+    ref = _one_group_per_frame(shape, fr)
+    f, nb = fr.c_struct(), C.c_size_t()
+    assert shape.lib.shape_frame_workspace_bytes(C.byref(f), C.byref(nb)) == shape.OK
+    ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda")
+    out = {k: torch.empty(v.shape, dtype=getattr(torch, str(v.dtype)), device="cuda")
+           for k, v in ref.items()}
+    rc = shape.lib.shape_frame_detect_ws(C.byref(f), 128, *(t.data_ptr() for t in out.values()),
+                                         ws.data_ptr(), nb.value, None)
+    assert rc == shape.OK
+    torch.cuda.synchronize()
+    for k in ref:
+        np.testing.assert_array_equal(g[k], ref[k], err_msg=k)
+        np.testing.assert_array_equal(out[k].cpu().numpy(), ref[k], err_msg=k)
