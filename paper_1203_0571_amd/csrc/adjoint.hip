@@ -4,7 +4,7 @@
 // With r_i = (d_i - m_i) / sigma the adjoint of pixel i is
 //   dL/dm_i = -(2 / sigma) r_i dL/dchi2,
 // and dL/dp_k = sum_i dL/dm_i dm_i/dp_k.  Render, Jacobian and sums are FP64
-// (adjoint_sweep.hpp for the Sersic stamps of large stamps and batches,
+// (adjoint_sweep.hpp for the Sersic stamps of a batch of one larger side,
 // sweep.hpp's FP64 instance for the others and for Moffat stamps, each a kernel
 // of its own so that neither holds the other's registers): the FP32 rounding of
 // the exponent b t is amplified where the gradient components cancel over the
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_tables_ker
 }
 
 // The stamps of one model, one wave per stamp (sweep.hpp in FP64): Moffat
-// stamps, and the Sersic stamps of batches that do not earn the tables.  With
+// stamps, and the Sersic stamps of batches that do not take the tables.  With
 // J^T J, FP16 stamps' rolled loops fit three waves per SIMD.
 template <int DT, int MODEL, bool GRAD, bool JTJ>
 __global__ __launch_bounds__(kWave, JTJ ? (DT == SHAPE_F32 ? 2 : 3) : 5) void chi2_kernel(
@@ -165,27 +165,24 @@ __global__ __launch_bounds__(kWave, JTJ ? (DT == SHAPE_F32 ? 2 : 3) : 5) void ch
   }
 }
 
-// Whether the Sersic stamps of a batch take the tables: from a mean area of 48 x
-// 48, or where the batch holds 3e7 pixels (but for the normal matrix of FP16
-// stamps, whose three waves per SIMD stay the faster there).  A stamp's own
-// tables and a workgroup's cost 600 instructions, which small stamps do not earn
-// back, nor batches too small to give a workgroup several stamps.  Time against
-// chi2_kernel's (chi^2, gradient, normal matrix): side 48 and up 0.5-0.99 at
-// every size; 12 to 37 above 3e7 pixels 0.80-1.02, 0.78-0.90, 0.85-0.99 (FP16
-// normal matrix 0.99-1.11); at 1.2e7 pixels 0.96-1.4, 0.86-1.11, 0.94-1.16; at
-// 3e6 1.1-2.1, 0.9-1.4, 1.05-1.44.
-template <int DT, bool JTJ>
-bool takes_tables(const shape_batch& b) {
-  const int64_t area = b.side ? b.n_pixels : b.n * ((int64_t)b.side0 * b.side0);
-  if (area >= b.n * (48 * 48)) return true;
-  return area >= 30000000 && !(JTJ && DT == SHAPE_F16_SCALED);
-}
+// Whether the Sersic stamps of a batch take the tables: those of a batch of one
+// side, from 48 on, however many, so that a stamp's results do not depend on its
+// batch.  A stamp's own tables and a workgroup's cost 600 instructions, which
+// small stamps earn back in large batches only.  Time against chi2_kernel's over
+// 16 to 20,000 stamps (chi^2, gradient, normal matrix; FP32 and FP16): side 48
+// 0.77-1.06, 0.73-0.95, 0.80-0.97; 52 to 64 0.72-1.08, 0.68-0.99, 0.74-1.01; 44
+// 0.83-1.14, 0.79-0.99, 0.88-1.08; 36 0.93-1.28, 0.86-1.16, 0.94-1.18; 28 1.02-1.47,
+// 0.90-1.27, 0.98-1.31.  Mixed sides would need both kernels, each passing over
+// the other's stamps (100 stamps of side 24 11 -> 14 us, 20,000 46 -> 60), or one
+// that holds both sweeps (20,000 46 -> 69).
+constexpr int kTablesSide = 48;
+bool takes_tables(const shape_batch& b) { return !b.side && b.side0 >= kTablesSide; }
 
 template <int DT, bool GRAD, bool JTJ>
 hipError_t launch_dt(const shape_batch& b, const float* params, const float* grad_chi2,
                      float* chi2, float* grad_p, float* jtj, float* jtr, hipStream_t stream) {
   const dim3 g((unsigned)(b.n < (1ll << 30) ? b.n : (1ll << 30))), t(kWave);
-  if (takes_tables<DT, JTJ>(b)) {
+  if (takes_tables(b)) {
     // chunks of up to kChi2Chunk stamps that still make 8,192 workgroups, a few
     // rounds over the card
     const int64_t most = b.n / 8192, chunk = most < 1 ? 1 : most > kChi2Chunk ? kChi2Chunk : most;

@@ -24,8 +24,8 @@
 // exp2 tables, one wave per stamp (us; chi^2 / with gradient / with the normal
 // matrix): 65,536 of 64 x 64 FP32 628 / 809 / 1,170 -> 510 / 679 / 1,034, FP16
 // 623 / 796 / 1,112 -> 483 / 651 / 984; 20,000 of 48 x 48 FP16 129 / 184 / 256 ->
-// 99 / 135 / 223; 8,000 of 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  Small
-// stamps in small batches keep that sweep (adjoint.hip).  40, 62 and 88 VALU
+// 99 / 135 / 223; 8,000 of 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  Smaller
+// stamps and mixed sides keep that sweep (adjoint.hip).  40, 62 and 88 VALU
 // instructions per pixel and 500 to 1,000 per stamp; the SIMDs issue on about
 // 90% of cycles.
 #pragma once
@@ -84,8 +84,8 @@ __device__ __forceinline__ double in_vgpr(double v) {
 
 // Parts of a column for each side: the count, of at most 8, whose items fill the
 // wave's lanes at the least cost, a row at 1 and an item's own work (column
-// constants, recombination) at 2 rows.  Sides 16, 32, 64 and 128 fill them
-// exactly; 48 takes 4 parts (3 rounds of 12 rows), 33 takes 5 (3 rounds of 7).
+// constants, recombination) at 2 rows.  Sides 64 and 128 fill them
+// exactly; 48 takes 4 parts (3 rounds of 12 rows), 100 takes 5 (8 rounds of 20).
 struct SersicParts {
   uint8_t of[kMaxSide + 1] = {};
   constexpr SersicParts() {

@@ -52,3 +52,61 @@ def test_a_frame_alone_and_among_many(shape, f16):
     for k, v in few.items():
         np.testing.assert_array_equal(many[k].reshape((70,) + v.shape),
                                       np.broadcast_to(v, (70,) + v.shape), err_msg=k)
+
+
+def _perfect_stamps(shape, side, f16, n=12):
+    """Stamps that hold their model to the last bit of the pixels, so that r is
+    rounding alone and the sums show every change of it."""
+    import oracle
+    rng = np.random.default_rng(side)
+    c = 0.5 * (side - 1)
+    p = np.empty((n, 8))
+    p[:, 0:2] = c + rng.uniform(-0.9, 0.9, (n, 2))
+    p[:, 2:4] = rng.uniform(-0.3, 0.3, (n, 2))
+    p[:, 4] = rng.uniform(0.08, 0.3, n) * side
+    p[:, 5] = rng.uniform(0.5, 5.0, n)
+    p[:, 6] = rng.uniform(1.0, 100.0, n)
+    p[:, 7] = rng.uniform(-5.0, 5.0, n)
+    p = p.astype(np.float32)
+    img = np.stack([oracle.model(side, q) for q in p.astype(np.float64)]).reshape(n, -1)
+    return p, (img * 2.0).astype(np.float16) if f16 else img.astype(np.float32)
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("side", [12, 16, 32, 47, 48, 64])
+def test_chi2_of_a_stamp_alone_and_among_many(shape, side, f16):
+    """12 stamps; the same in a batch of over 3e7 pixels; with a side array, alone
+    and in a buffer of 128 x 128 pixels a stamp, beside larger stamps."""
+    import torch
+    p, pix = _perfect_stamps(shape, side, f16)
+    n, area = len(p), side * side
+    t, pt = torch.from_numpy(pix).cuda(), torch.from_numpy(p).cuda()
+
+    def batch(pixels, k, **kw):
+        return shape.DeviceBatch(pixels=pixels, sigma=torch.full((k,), 1e-6, device="cuda"),
+                                 scale=torch.full((k,), 0.5, device="cuda") if f16 else None, **kw)
+
+    def outputs(db, params, pick):
+        out = dict(value=shape.chi2_fwd(db, params))
+        for want in (False, True):
+            for key, v in shape.chi2_bwd(db, params, want_normal=want).items():
+                if v is not None:
+                    out["%s %d" % (key, want)] = v
+        return {key: v[pick].cpu().numpy() for key, v in out.items()}
+
+    alone = outputs(batch(t.reshape(-1), n, side0=side), pt, slice(0, n))
+    k = 30_000_000 // (n * area) + 1
+    many = outputs(batch(t.repeat(k, 1).reshape(-1), n * k, side0=side), pt.repeat(k, 1),
+                   slice(n * (k - 1), n * k))
+    i = torch.arange(n, device="cuda")
+    sided = outputs(batch(t.reshape(-1), n, offsets=i * area, sides=(i * 0 + side).int()), pt,
+                    slice(0, n))
+    # the stamps first, then as many again of 128 x 128
+    big = torch.zeros(2 * n * 128 * 128, dtype=t.dtype, device="cuda")
+    big[:n * area] = t.reshape(-1)
+    mixed = outputs(batch(big, 2 * n, offsets=torch.cat([i * area, n * area + i * 128 * 128]),
+                          sides=torch.cat([i * 0 + side, i * 0 + 128]).int()),
+                    pt.repeat(2, 1), slice(0, n))
+    for key, v in alone.items():
+        np.testing.assert_array_equal(many[key], v, err_msg=key)
+        np.testing.assert_array_equal(mixed[key], sided[key], err_msg=key)
