@@ -17,19 +17,6 @@ namespace {
 #ifndef SHAPE_FIT_STAGE_F16
 #define SHAPE_FIT_STAGE_F16 1
 #endif
-template <int DT, int MODEL, uint32_t MASK, int LAYOUT, bool PROF>
-__device__ __forceinline__ void fit_one(const shape_batch& b, const KOpts& o, const Stamp& st,
-                                        const float* p_init, const float* rec, int64_t s,
-                                        LmShared& W, float* p_out, float* chi2, float* perr,
-                                        int32_t* iters, uint32_t* status, int32_t* sweeps,
-                                        int tid) {
-  lm_start<DT, MODEL, MASK, 1, LAYOUT>(b, o, st, p_init, rec, s, W, nullptr, tid);
-  while (!W.L.done && W.L.it < o.max_iter_lm)
-    lm_iterate<DT, MODEL, MASK, 1, LAYOUT, PROF>(b, o, st, W, nullptr, tid);
-  lm_finish<MODEL, MASK>(o, st, W.L, W.sums[W.cur], s, p_out, chi2, perr, iters, status, sweeps,
-                         tid);
-}
-
 template <int DT, int MODEL, uint32_t MASK, int LAYOUT, bool PROF = true>
 __global__ __launch_bounds__(kWave, SHAPE_FIT_WAVES_PER_SIMD) void fit_kernel(
     shape_batch b, KOpts o, const float* p_init, const float* rec, float* p_out, float* chi2,
@@ -67,20 +54,20 @@ __global__ __launch_bounds__(kWave, SHAPE_FIT_WAVES_PER_SIMD) void fit_kernel(
       bl.pixels = lds_px;
       Stamp sl = st;
       sl.off = 0;
-      fit_one<DT, MODEL, MASK, LAYOUT, PROF>(bl, o, sl, p_init, rec, s, W, p_out, chi2, perr,
-                                             iters, status, sweeps, tid);
+      lm_fit<DT, MODEL, MASK, 1, LAYOUT, PROF>(bl, o, sl, p_init, rec, s, W, p_out, chi2, perr,
+                                               iters, status, sweeps, tid);
     } else if constexpr (LAYOUT == kLayoutSegs) {
       // each of the two forms with an LM loop of its own: in one loop that held
       // both sweeps, each spilled for the other
       if (st.side >= kSegsMinSide)
-        fit_one<DT, MODEL, MASK, kLayoutSegsOnly, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
-                                                        perr, iters, status, sweeps, tid);
+        lm_fit<DT, MODEL, MASK, 1, kLayoutSegsOnly, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
+                                                          perr, iters, status, sweeps, tid);
       else
-        fit_one<DT, MODEL, MASK, kLayoutAny, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
-                                                   iters, status, sweeps, tid);
+        lm_fit<DT, MODEL, MASK, 1, kLayoutAny, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
+                                                     perr, iters, status, sweeps, tid);
     } else {
-      fit_one<DT, MODEL, MASK, LAYOUT, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
-                                             iters, status, sweeps, tid);
+      lm_fit<DT, MODEL, MASK, 1, LAYOUT, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
+                                               iters, status, sweeps, tid);
     }
     __syncthreads();  // W (and the staged stamp) are reused by the next stamp of this wave
   }
@@ -142,7 +129,7 @@ hipError_t launch_fit_dt(const shape_batch& b, const KOpts& o, const float* p_in
 hipError_t launch_fit(const shape_batch& b, const KOpts& o, const float* p_init, const float* rec,
                       float* p_out, float* chi2, float* perr, int32_t* iters, uint32_t* status,
                       int32_t* sweeps, hipStream_t stream) {
-  if (fit_takes_split(b))
+  if (fit_takes_split(b, o))
     return launch_fit_split(b, o, p_init, rec, p_out, chi2, perr, iters, status, sweeps, stream);
   if (b.dtype == SHAPE_F32)
     return launch_fit_dt<SHAPE_F32>(b, o, p_init, rec, p_out, chi2, perr, iters, status, sweeps,

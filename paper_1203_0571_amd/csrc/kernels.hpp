@@ -16,7 +16,7 @@ hipError_t launch_fit(const shape_batch& b, const KOpts& o, const float* p_init,
                       int32_t* sweeps, hipStream_t stream);
 // The same results with four waves per stamp, for the batches fit_takes_split
 // names (launch_fit calls it).
-bool fit_takes_split(const shape_batch& b);
+bool fit_takes_split(const shape_batch& b, const KOpts& o);
 hipError_t launch_fit_split(const shape_batch& b, const KOpts& o, const float* p_init,
                             const float* rec, float* p_out, float* chi2, float* perr,
                             int32_t* iters, uint32_t* status, int32_t* sweeps, hipStream_t stream);

@@ -673,4 +673,18 @@ __device__ __forceinline__ void lm_finish(const KOpts& o, const Stamp& st, LmSta
   }
 }
 
+// The whole fit of one stamp: start, LM trials until done, outputs.
+template <int DT, int MODEL, uint32_t MASK, int TEAM, int LAYOUT, bool PROF>
+__device__ __forceinline__ void lm_fit(const shape_batch& b, const KOpts& o, const Stamp& st,
+                                       const float* p_init, const float* rec, int64_t s,
+                                       LmShared& W, float* p_out, float* chi2, float* perr,
+                                       int32_t* iters, uint32_t* status, int32_t* sweeps,
+                                       int tid) {
+  lm_start<DT, MODEL, MASK, TEAM, LAYOUT>(b, o, st, p_init, rec, s, W, nullptr, tid);
+  while (!W.L.done && W.L.it < o.max_iter_lm)
+    lm_iterate<DT, MODEL, MASK, TEAM, LAYOUT, PROF>(b, o, st, W, nullptr, tid);
+  lm_finish<MODEL, MASK>(o, st, W.L, W.sums[W.cur], s, p_out, chi2, perr, iters, status, sweeps,
+                         tid);
+}
+
 }  // namespace shape

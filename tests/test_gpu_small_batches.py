@@ -188,3 +188,57 @@ def test_centroid_start_is_the_first_maximum(shape, side, storage):
         # FP64 sums of up to 2^14 terms against an exact total, then FP32
         np.testing.assert_allclose(rec[s, 5], want, rtol=1e-6, atol=1e-6)
         np.testing.assert_allclose(rec[s, 7], c[-1], rtol=1e-6)
+
+
+def _time(f, repeat=5):
+    """Shortest of `repeat` passes, in ms."""
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(repeat):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(4):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) / 4)
+    return best
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+def test_fit_of_some_split_stamps(shape, storage):
+    """1,000 stamps of mixed sides, of which the largest take four waves each,
+    against one wave each (a larger batch)."""
+    b = synth.make("uneven", count=1000, storage=storage)
+    db = shape.DeviceBatch.from_host(b, "cuda:0", uniform=False)
+    assert b.sides.max() > 1.5 * np.sqrt(np.mean(b.sides.astype(float) ** 2)) + 8
+    db.sides[8] = 3
+    db.sigma[10] = -1.0
+    db.pixels[int(b.offsets[11])] = float("nan")
+    large = _repeat(shape, db, SPLIT_LIMIT + 1)
+    for kw in (dict(), dict(free_mask=shape.MASK_SIZE), dict(max_iter_lm=1)):
+        _same_fits(shape, db, large, shape.default_opts(**kw))
+    db.model = large.model = None
+    _same_fits(shape, db, large, shape.default_opts(free_mask=shape.MASK_SIZE, linear_init=0))
+
+
+def test_stamps_of_equal_sides_cost_the_same_with_a_side_array(shape):
+    """Of 4,096 stamps of 24 x 24 none sets the pace: given with offsets and sides
+    (as cut-outs are) they take little more than a batch of one side (1.23 times;
+    four waves for each stamp took 2.16 times)."""
+    import torch
+    b = synth.make("sersic64", count=64)
+    w, side, n = int(b.sides[0]), 24, 4096
+    c = (w - side) // 2
+    img = b.pixels.reshape(64, w, w)[:, c:c + side, c:c + side].astype(np.float32)
+    pix = torch.from_numpy(np.ascontiguousarray(img)).cuda().repeat(n // 64, 1, 1).reshape(-1)
+    sigma = torch.from_numpy(b.sigma[:64].astype(np.float32)).cuda().repeat(n // 64)
+    one = shape.DeviceBatch(pixels=pix, sigma=sigma, side0=side)
+    sided = shape.DeviceBatch(pixels=pix, sigma=sigma,
+                              offsets=torch.arange(n, device="cuda") * side * side,
+                              sides=torch.full((n,), side, dtype=torch.int32, device="cuda"))
+    rec, _, _ = shape.moments(one, shape.centroid(one)[0])
+    t1 = _time(lambda: shape.fit_sersic(one, rec=rec))
+    t2 = _time(lambda: shape.fit_sersic(sided, rec=rec))
+    assert t2 < 1.6 * t1, (t1, t2)
