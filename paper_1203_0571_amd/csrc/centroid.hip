@@ -749,7 +749,7 @@ centroid_any_kernel(shape_batch b, KOpts o, float* rec, int32_t* iters, uint32_t
 }
 
 // Every form in one launch, for a batch of mixed sides that does not fill the
-// card (kOneLaunch): workgroup s takes stamp s.  Bound by the slowest stamp's
+// card (kOneLaunchCentroid): workgroup s takes stamp s.  Bound by the slowest stamp's
 // iterations; three launches ran one after the other.
 template <int DT>
 __global__ __launch_bounds__(4 * kWave, SHAPE_CENTROID_ANY_WAVES_PER_SIMD) void
@@ -802,7 +802,7 @@ void launch_dtype(const shape_batch& b, const KOpts& o, float* rec, int32_t* ite
   // workgroup.  Mixed sides: every form, each workgroup looking at a chunk of
   // stamps and taking those of its form.
   const bool mixed = b.side != nullptr;
-  if (mixed && b.n <= kOneLaunch) {
+  if (mixed && b.n <= kOneLaunchCentroid) {
     hipLaunchKernelGGL((centroid_mixed_kernel<DT>), dim3((unsigned)b.n), dim3(4 * kWave), 0, stream,
                        b, o, rec, iters, status);
     return;

@@ -619,7 +619,7 @@ void launch_dtype(const shape_batch& b, const KOpts& o, const float* rec_in, flo
   // workgroup.  Mixed sides: every form, each workgroup looking at a chunk of
   // stamps and taking those of its form.
   const bool mixed = b.side != nullptr;
-  if (mixed && b.n <= kOneLaunch) {
+  if (mixed && b.n <= kOneLaunchMoments) {
     hipLaunchKernelGGL((moments_mixed_kernel<DT>), dim3((unsigned)b.n), dim3(4 * kWave), 0, stream,
                        b, o, rec_in, rec_out, iters, status);
     return;

@@ -132,12 +132,12 @@ inline int chunk_of(int64_t n) {
 
 // Up to this many stamps of mixed sides one launch takes every form: a
 // workgroup of four waves per stamp, of which a stamp's team stays and the
-// other waves end at once.  Measured, sides log-uniform over 16..128, one
-// launch against three (us): 100 stamps centroid 35 / 111, moments 48 / 141;
-// 2,000 stamps 67 / 149, 107 / 225; 32,000 stamps 560 / 746, 867 / 999;
-// 200,000 stamps 3,242 / 3,249, 5,088 / 4,576 (the waves that end at once hold
-// their registers meanwhile).
-constexpr int64_t kOneLaunch = 65536;
+// other waves end at once, though they hold their registers meanwhile (more of
+// them in the moments).  Measured, one launch against three (us): sides log-uniform
+// over 16..128, 100 stamps centroid 35 / 111, moments 48 / 141; 16,384 255 / 409, 447 /
+// 575; 49,152 718 / 941, 1,263 / 1,351; all of side 24, 16,384 74 / 79, 218 / 218;
+// 24,576 105 / 108, 309 / 291; 49,152 199 / 203, 577 / 519; 65,536 262 / 238, 755 / 604.
+constexpr int64_t kOneLaunchCentroid = 49152, kOneLaunchMoments = 16384;
 
 // Which stamps of the chunk [s0, s0 + chunk) (chunk <= 64) a form takes, as
 // a bit mask (team_takes); stamps that cannot be processed go to the

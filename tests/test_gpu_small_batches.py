@@ -242,3 +242,22 @@ def test_stamps_of_equal_sides_cost_the_same_with_a_side_array(shape):
     t1 = _time(lambda: shape.fit_sersic(one, rec=rec))
     t2 = _time(lambda: shape.fit_sersic(sided, rec=rec))
     assert t2 < 1.6 * t1, (t1, t2)
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 49152, 49153])
+def test_mixed_sides_at_the_limits_of_one_launch(shape, n):
+    """The last batch that centroid (49,152) and moments (16,384) take in one
+    launch, and the first of a launch per form, against a small one."""
+    import torch
+    b = synth.make("uneven", count=256)
+    db = shape.DeviceBatch.from_host(b, "cuda:0", uniform=False)
+    db.sides[8], db.sigma[10] = 3, -1.0
+    got = []
+    for batch in (db, _repeat(shape, db, n)):
+        rec, it, st = shape.centroid(batch)
+        out = (rec, it, st) + tuple(shape.moments(batch, rec))
+        torch.cuda.synchronize()
+        got.append([t.cpu().numpy() for t in out])
+    idx = np.arange(n) % db.n
+    for a, c in zip(*got):
+        np.testing.assert_array_equal(c, a[idx])
