@@ -54,19 +54,19 @@ __global__ __launch_bounds__(kWave, SHAPE_FIT_WAVES_PER_SIMD) void fit_kernel(
       bl.pixels = lds_px;
       Stamp sl = st;
       sl.off = 0;
-      lm_fit<DT, MODEL, MASK, 1, LAYOUT, PROF>(bl, o, sl, p_init, rec, s, W, p_out, chi2, perr,
+      lm_fit<DT, MODEL, MASK, 1, LAYOUT | kLayoutFloorFree, PROF>(bl, o, sl, p_init, rec, s, W, p_out, chi2, perr,
                                                iters, status, sweeps, tid);
     } else if constexpr (LAYOUT == kLayoutSegs) {
       // each of the two forms with an LM loop of its own: in one loop that held
       // both sweeps, each spilled for the other
       if (st.side >= kSegsMinSide)
-        lm_fit<DT, MODEL, MASK, 1, kLayoutSegsOnly, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
+        lm_fit<DT, MODEL, MASK, 1, kLayoutSegsOnly | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
                                                           perr, iters, status, sweeps, tid);
       else
-        lm_fit<DT, MODEL, MASK, 1, kLayoutAny, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
+        lm_fit<DT, MODEL, MASK, 1, kLayoutAny | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
                                                      perr, iters, status, sweeps, tid);
     } else {
-      lm_fit<DT, MODEL, MASK, 1, LAYOUT, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
+      lm_fit<DT, MODEL, MASK, 1, LAYOUT | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
                                                iters, status, sweeps, tid);
     }
     __syncthreads();  // W (and the staged stamp) are reused by the next stamp of this wave

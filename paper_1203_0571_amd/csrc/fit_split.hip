@@ -112,10 +112,10 @@ __global__ __launch_bounds__(kWave * kSplitWaves, 4) void fit_uneven_kernel(
       lm_fit<DT, M, MASK, kSplit, kLayoutSegsOnly, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
                                                          perr, iters, status, sweeps, tid);
     else if (st.side >= kSegsMinSide)
-      lm_fit<DT, M, MASK, 1, kLayoutSegsOnly, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
+      lm_fit<DT, M, MASK, 1, kLayoutSegsOnly | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
                                                     iters, status, sweeps, tid);
     else
-      lm_fit<DT, M, MASK, 1, kLayoutAny, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
+      lm_fit<DT, M, MASK, 1, kLayoutAny | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
                                                iters, status, sweeps, tid);
   };
   if (!PROF || st.model == SHAPE_SERSIC)

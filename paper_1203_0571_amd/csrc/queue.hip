@@ -680,6 +680,7 @@ __global__ __launch_bounds__(kWave* TEAM, 4) void drain_kernel(shape_batch b, KO
       drain_store<TEAM>(v, r, W[0], tid);
     }
   }
+  constexpr int FORM = LAYOUT == kLayoutRows ? LAYOUT | kLayoutFloorFree : LAYOUT;
   const int c = cls(MODEL, false);
   const uint32_t cnt = v.hdr->count[which][c];
   for (;;) {
@@ -701,13 +702,13 @@ __global__ __launch_bounds__(kWave* TEAM, 4) void drain_kernel(shape_batch b, KO
       bl.pixels = lds_px;
       Stamp sl = st;
       sl.off = 0;
-      lm_sweep_judge<DT, MODEL, MASK, 1, LAYOUT>(bl, o, sl, W[wave], nullptr, lane);
+      lm_sweep_judge<DT, MODEL, MASK, 1, FORM>(bl, o, sl, W[wave], nullptr, lane);
       while (!W[wave].L.done && W[wave].L.it < o.max_iter_lm)
-        lm_iterate<DT, MODEL, MASK, 1, LAYOUT>(bl, o, sl, W[wave], nullptr, lane);
+        lm_iterate<DT, MODEL, MASK, 1, FORM>(bl, o, sl, W[wave], nullptr, lane);
     } else {
-      lm_sweep_judge<DT, MODEL, MASK, 1, LAYOUT>(b, o, st, W[wave], nullptr, lane);
+      lm_sweep_judge<DT, MODEL, MASK, 1, FORM>(b, o, st, W[wave], nullptr, lane);
       while (!W[wave].L.done && W[wave].L.it < o.max_iter_lm)
-        lm_iterate<DT, MODEL, MASK, 1, LAYOUT>(b, o, st, W[wave], nullptr, lane);
+        lm_iterate<DT, MODEL, MASK, 1, FORM>(b, o, st, W[wave], nullptr, lane);
     }
     drain_store<1>(v, r, W[wave], lane);
   }

@@ -561,6 +561,9 @@ constexpr int kLayoutSegsStaged = 4;
 // kLayoutSegsOnly: the segments for a stamp known to take them, without the
 // walk's code.
 constexpr int kLayoutSegsOnly = 5;
+// kLayoutFloorFree: with kLayoutRows, kLayoutAny or kLayoutSegsOnly, two copies of
+// the loops, of which one has no test for the model's floor (clear_of_floor).
+constexpr int kLayoutFloorFree = 16;
 
 __host__ __device__ inline constexpr bool rows_layout_fits(int side) {
   return side == 8 || side == 16 || side == 32 || side == 64;
@@ -614,10 +617,11 @@ __host__ __device__ constexpr bool in_sums(uint32_t sums, int k, int l) {   // k
 // JTJ = false leaves the J^T J sums at zero (callers that need only chi^2
 // and J^T r); SUMS: the kinds of sums formed (the others are left at zero).
 template <int DT, int MODEL, uint32_t EM, int STRIDE = kWave, typename T = float,
-          int LAYOUT = kLayoutAny, bool JTJ = true, uint32_t SUMS = kSumsAll>
+          int FORM = kLayoutAny, bool JTJ = true, uint32_t SUMS = kSumsAll>
 __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, const Trial<T>& t,
                              Acc<EM, T>& acc, int tid = -1, void* stage = nullptr) {
   using A = Arith<T>;
+  constexpr int LAYOUT = FORM & ~kLayoutFloorFree;
   constexpr int kFlush = sizeof(T) == 4 ? SHAPE_SWEEP_FLUSH : 0;
   constexpr bool kGrad = (SUMS & kSumsGradient) != 0u;   // chi^2 and J^T r
   acc.c2 = 0.0;
@@ -794,14 +798,17 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
       }
     }
   };
-  // A wave alone on its stamp takes a copy of the loops without the floor's
-  // comparison and selections (3 of 55 to 100 VALU per pixel) where no pixel
-  // needs them, nearly always: fit of 262,144 stamps of 64 x 64 FP16 17.7 ->
-  // 17.1 ms.  Not where one LM loop holds the walk and the segments (the two
-  // copies of both spill: 15.4 -> 15.6 ms on 200,000 stamps of mixed sides).
-  constexpr bool kClear = STRIDE == kWave && sizeof(T) == 4 && SUMS == kSumsAll &&
-                          (LAYOUT == kLayoutRows || LAYOUT == kLayoutAny ||
-                           LAYOUT == kLayoutSegsOnly);
+  // The fused fit takes a copy of the loops without the floor's comparison and
+  // selections (3 of 55 to 100 VALU per pixel) where no pixel needs them, nearly
+  // always: fit of 262,144 stamps of 64 x 64 FP16 17.7 -> 17.1 ms.  Not where one LM
+  // loop holds the walk and the segments (the two copies of both spill: 15.4 ->
+  // 15.6 ms on 200,000 stamps of mixed sides), nor in the queue's steps and its
+  // drain of walked stamps (64 x 64 FP32 6.25 -> 6.35 ms for six steps of 100,000, 48
+  // x 48 drain 6.34 -> 6.64 ms); the drain of row stamps gains (7.88 -> 7.78 ms).
+  constexpr bool kClear = (FORM & kLayoutFloorFree) != 0;
+  static_assert(!kClear || (STRIDE == kWave && sizeof(T) == 4 && SUMS == kSumsAll &&
+                            (LAYOUT == kLayoutRows || LAYOUT == kLayoutAny ||
+                             LAYOUT == kLayoutSegsOnly)), "a wave alone on its stamp");
   auto either = [&](auto&& loops) {
     if constexpr (kClear) {
       if (clear_of_floor(t, st.side)) return loops(std::false_type());
@@ -1042,6 +1049,11 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
             const int sg = s0 + lane;
             const bool on = sg < S;
             const int g = on ? sg / W : 0, j = on ? sg - g * W : 0, r0 = g * kSegRows;
+            // opaque, so that the tests below stay one by one: known to imply each
+            // other they became nested branches, each load sunk into its own (queue
+            // steps of 100 x 100 stamps 6% slower, 1 to 13 more spills)
+            int rows = W;
+            asm volatile("" : "+s"(rows));
             const Column<T> col(t, (T)j - t.x0);
             // the segment's pixels (rows past the stamp read its last row and are
             // skipped below), loaded back to back
@@ -1053,7 +1065,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
             }
 #pragma unroll
             for (int q = 0; q < kSegRows; ++q) {
-              if (on && r0 + q < W) {
+              if (on && r0 + q < rows) {
                 const T u2 = (T)(r0 + q) - t.y0;
                 pixel(std::true_type(), flr, d[q], col.R2(t, u2), col.n1(t, u2), col.n2(t, u2),
                       col.P2(t, u2), col.P3(t, u2));
