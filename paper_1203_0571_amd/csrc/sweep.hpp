@@ -595,16 +595,6 @@ inline int single_wave_layout(const shape_batch& b, int model) {
 #define SHAPE_SWEEP_FLUSH 8
 #endif
 
-// Whether a sweep over a stamp of side `side` adds the columns' own sums with
-// one rounding (add_product): the FP32 instance of each layout.
-template <int DT, int LAYOUT>
-__host__ __device__ constexpr bool sums_fused(int side, bool moments) {
-  if (LAYOUT == kLayoutRows)
-    return (moments || DT == SHAPE_F32) && side * side / kWave % 8 == 0;
-  return (LAYOUT == kLayoutSegs || LAYOUT == kLayoutSegsStaged || LAYOUT == kLayoutSegsOnly) &&
-         side >= kSegsMinSide;
-}
-
 // The kinds of sums a sweep forms: J^T J of (x0, y0, e1, e2) among themselves;
 // of those against (size, n, I0); of (size, n, I0) among themselves and all
 // sums of the sky column; chi^2 and J^T r.
@@ -839,7 +829,7 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     // spare, are unrolled in either storage.
     constexpr bool kPart = SUMS != kSumsAll;
     constexpr bool kUnroll = kPart || (DT == SHAPE_F32 && (sizeof(T) == 4 || EM == 0u || JTJ));
-    using RunFused = std::bool_constant<kMom || DT == SHAPE_F32>;   // sums_fused of whole runs
+    using RunFused = std::bool_constant<kMom || DT == SHAPE_F32>;   // add_product in whole runs
     const bool blocked = kUnroll && nstep % kRun == 0;   // wave-uniform
     // R^2 S along the column (the moment form's units)
     const T qas = A::uni(t.qa * mu.S), qbs = col.qb * mu.S, qcs = col.qc * mu.S;
