@@ -96,8 +96,9 @@ template <int DT, bool GRAD, bool JTJ>
 __global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_tables_kernel(
     shape_batch b, const float* params, const float* grad_chi2, float* chi2, float* grad_p,
     float* jtj, float* jtr, int chunk) {
-  __shared__ SersicTables tab;
+  __shared__ SersicTables<kChi2Chunk<GRAD>> tab;
   const int lane = threadIdx.x;
+  bool general = false;   // whether the general sweep's tables are filled
   sersic_tables_fill(tab, lane);
   for (int64_t s0 = (int64_t)blockIdx.x * chunk; s0 < b.n; s0 += (int64_t)gridDim.x * chunk) {
     const int n = (int)(b.n - s0 < chunk ? b.n - s0 : chunk);
@@ -112,7 +113,7 @@ __global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_tables_ker
           write_nan<GRAD>(s, chi2, grad_p, jtj, jtr);
         } else {
           tab.t[lane] = make_trial<double, false>(p, SHAPE_SERSIC, 0.0);
-          todo = sersic_covered(p, st.side) ? kCovered : kSeries;
+          todo = sersic_covered(p, st.side) ? kCovered : kGeneral;
         }
       }
       tab.todo[lane] = todo;
@@ -124,10 +125,16 @@ __global__ __launch_bounds__(kWave, JTJ ? 2 : GRAD ? 3 : 5) void chi2_tables_ker
       if (todo == kSkip) continue;
       const Stamp st = stamp_info(b, s0 + i);
       Acc<GRAD ? 0xFFu : 0u, double> acc;
-      if (todo == kCovered)
-        sersic_sweep<DT, GRAD, JTJ, true>(b, st, tab, tab.t[i], lane, acc);
-      else
-        sersic_sweep<DT, GRAD, JTJ, false>(b, st, tab, tab.t[i], lane, acc);
+      // (expected: else the general sweep's registers spill in the covered one)
+      if (__builtin_expect(todo == kCovered, 1)) {
+        sersic_sweep<DT, GRAD, JTJ>(b, st, tab, tab.t[i], lane, acc);
+      } else {
+        if (!general) f64_tables_fill(lane, kWave);
+        general = true;
+        wave_sync();
+        sweep<DT, SHAPE_SERSIC, GRAD ? 0xFFu : 0u, kWave, double, kLayoutAny, JTJ>(b, st, tab.t[i],
+                                                                                  acc);
+      }
       write_sums<GRAD, JTJ>(acc, st, s0 + i, grad_chi2, chi2, grad_p, jtj, jtr, lane);
     }
   }
@@ -170,7 +177,7 @@ __global__ __launch_bounds__(kWave, JTJ ? (DT == SHAPE_F32 ? 2 : 3) : 5) void ch
 // batch.  A stamp's own tables and a workgroup's cost 600 instructions, which
 // small stamps earn back in large batches only.  Time against chi2_kernel's over
 // 16 to 20,000 stamps (chi^2, gradient, normal matrix; FP32 and FP16): side 48
-// 0.77-1.06, 0.73-0.95, 0.80-0.97; 52 to 64 0.72-1.08, 0.68-0.99, 0.74-1.01; 44
+// 0.75-1.05, 0.70-0.86, 0.76-0.97; 52 to 64 0.73-1.06, 0.70-0.86, 0.76-0.95; 44
 // 0.83-1.14, 0.79-0.99, 0.88-1.08; 36 0.93-1.28, 0.86-1.16, 0.94-1.18; 28 1.02-1.47,
 // 0.90-1.27, 0.98-1.31.  Mixed sides would need both kernels, each passing over
 // the other's stamps (100 stamps of side 24 11 -> 14 us, 20,000 46 -> 60), or one
@@ -185,7 +192,8 @@ hipError_t launch_dt(const shape_batch& b, const float* params, const float* gra
   if (takes_tables(b)) {
     // chunks of up to kChi2Chunk stamps that still make 8,192 workgroups, a few
     // rounds over the card
-    const int64_t most = b.n / 8192, chunk = most < 1 ? 1 : most > kChi2Chunk ? kChi2Chunk : most;
+    constexpr int64_t most = kChi2Chunk<GRAD>;
+    const int64_t fair = b.n / 8192, chunk = fair < 1 ? 1 : fair > most ? most : fair;
     const int64_t groups = (b.n + chunk - 1) / chunk, cap = 1ll << 25;
     hipLaunchKernelGGL((chi2_tables_kernel<DT, GRAD, JTJ>),
                        dim3((unsigned)(groups < cap ? groups : cap)), t, 0, stream, b, params,

@@ -22,9 +22,9 @@
 //
 // Measured against the lane-stride or row-layout sweep by 64-point log2 and
 // exp2 tables, one wave per stamp (us; chi^2 / with gradient / with the normal
-// matrix): 65,536 of 64 x 64 FP32 628 / 809 / 1,170 -> 510 / 679 / 1,034, FP16
-// 623 / 796 / 1,112 -> 483 / 651 / 984; 20,000 of 48 x 48 FP16 129 / 184 / 256 ->
-// 99 / 135 / 223; 8,000 of 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  Smaller
+// matrix): 65,536 of 64 x 64 FP32 628 / 809 / 1,170 -> 463 / 656 / 961, FP16
+// 623 / 796 / 1,112 -> 433 / 614 / 937; 20,000 of 48 x 48 FP16 129 / 184 / 256 ->
+// 97 / 130 / 213; 8,000 of 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  Smaller
 // stamps and mixed sides keep that sweep (adjoint.hip).  40, 62 and 88 VALU
 // instructions per pixel and 500 to 1,000 per stamp; the SIMDs issue on about
 // 90% of cycles.
@@ -39,13 +39,16 @@ constexpr int kPowExp = 64;         // binary exponents kPowExpLo .. + 63
 constexpr int kPowExpLo = -25;
 constexpr int kAhead = 4;           // rows loaded ahead of their use
 
-// Stamps a workgroup takes: a stamp's constants (b(n) by its series, a
+// Stamps a workgroup takes at most: a stamp's constants (b(n) by its series, a
 // logarithm, reciprocals: some 400 instructions and a chain of loads) are
-// formed for all of them at once, one per lane.
-constexpr int kChi2Chunk = 8;
-enum SersicDo { kSkip = 0, kCovered = 1, kSeries = 2 };
+// formed for all of them at once, one per lane.  Four for chi^2 alone, whose five
+// waves per SIMD leave a workgroup 8 KB of LDS.
+template <bool GRAD>
+constexpr int kChi2Chunk = GRAD ? 8 : 4;
+enum SersicDo { kSkip = 0, kCovered = 1, kGeneral = 2 };
 
 // LDS of the sweep: the tables every stamp uses, and the stamp's.
+template <int CHUNK>
 struct SersicTables {
   double ex[kF64Tab];               // 2^(j / 64) / 24
   // 2 / c_j, log2 c_j - 1 and the stamp's c_j^beta (one address for all three)
@@ -55,11 +58,12 @@ struct SersicTables {
   double E[kPowExp];                // the stamp's, at the exponent's low bits
   // the constants of a chunk of stamps, formed one stamp per lane, and what to
   // do with each (SersicDo)
-  Trial<double> t[kChi2Chunk];
-  int todo[kChi2Chunk];
+  Trial<double> t[CHUNK];
+  int todo[CHUNK];
 };
 
-__device__ __forceinline__ void sersic_tables_fill(SersicTables& tab, int lane) {
+template <int CHUNK>
+__device__ __forceinline__ void sersic_tables_fill(SersicTables<CHUNK>& tab, int lane) {
   for (int j = lane; j < kF64Tab; j += kWave)
     tab.ex[j] = exp2_series(j / (double)kF64Tab) * (1.0 / 24.0);
   for (int j = lane; j < kPowTab; j += kWave) {
@@ -105,13 +109,17 @@ struct SersicParts {
 };
 static __constant__ const SersicParts kSersicParts;
 
-// Whether the tables cover the stamp: positive sizes in the ranges the series
-// are cut for, and R^2 of every pixel between 2^-24 (above the model's floor)
-// and 2^38.  The ellipse's axes bound R^2 by |u|^2 (1 - e) / (1 + e) and
-// |u|^2 (1 + e) / (1 - e).  Other stamps take the general sweep.
+// Whether the tables and the moment form cover the stamp: positive sizes in the
+// ranges the series are cut for, and R^2 of every pixel between 2^-24 (above the
+// model's floor) and 2^38.  The ellipse's axes bound R^2 by |u|^2 (1 - e) / (1 + e)
+// and |u|^2 (1 + e) / (1 - e).  Where the ellipse is long, the shape columns' sums
+// cancel in the forms' coefficients: J^T J from the moments is good to its FP32
+// rounding (6e-8) up to e = 0.95, but off by up to 3e-7 of an entry at 0.98, 2e-5 at
+// 0.995 and 1e-2 at 0.9995.  Other stamps take the general sweep, whose columns are
+// formed per pixel (6e-8 at every e).
 __device__ __forceinline__ bool sersic_covered(const double* p, int side) {
   const double e = sqrt(p[2] * p[2] + p[3] * p[3]);
-  if (!(e < 0.999 && p[4] >= 1e-3 && p[4] <= 1e5 && p[5] >= 0.1 && p[5] <= 20.0)) return false;
+  if (!(e < 0.95 && p[4] >= 1e-3 && p[4] <= 1e5 && p[5] >= 0.1 && p[5] <= 20.0)) return false;
   const double ratio = (1.0 - e) / (1.0 + e), last = side - 1;
   const double dx = p[0] - fmin(fmax(rint(p[0]), 0.0), last);
   const double dy = p[1] - fmin(fmax(rint(p[1]), 0.0), last);
@@ -119,44 +127,30 @@ __device__ __forceinline__ bool sersic_covered(const double* p, int side) {
   return (dx * dx + dy * dy) * ratio >= 0x1p-24 && mx * mx + my * my <= 0x1p38 * ratio;
 }
 
-// The powers of a pixel at R^2: t, t / R^2 (0 under the model's floor, where
-// the centre and shape derivatives are taken as 0), m0 and log2 R^2.
+// The powers of a pixel at R^2: t, t / R^2, m0 and log2 R^2.
 struct SersicPowers {
   double t, tr, m0, L;
 };
 
-// Any parameters and any R^2, by the full series: a few times slower.
-__device__ __forceinline__ SersicPowers sersic_powers(const Trial<double>& t, double R2) {
-  SersicPowers q;
-  const bool floored = R2 < Arith<double>::kR2Floor;
-  R2 = floored ? Arith<double>::kR2Floor : R2;
-  q.L = log2_series(R2);
-  q.t = exp2_series(fma(q.L, t.ha, t.hc));
-  q.tr = floored ? 0.0 : q.t / R2;
-  q.m0 = exp2_series(t.nb2 * q.t);
-  return q;
-}
-
-// The wave's sums over a Sersic stamp: c2 = sum r^2, g = J^T r (GRAD), A = J^T J
-// (JTJ), per lane.  COVERED: the stamp is one that the tables cover.
-template <int DT, bool GRAD, bool JTJ, bool COVERED>
+// The wave's sums over a Sersic stamp that the tables cover: c2 = sum r^2, g = J^T r
+// (GRAD), A = J^T J (JTJ), per lane.
+template <int DT, bool GRAD, bool JTJ>
 __device__ __forceinline__ void sersic_sweep(const shape_batch& b, const Stamp& st,
-                                             SersicTables& tab, const Trial<double>& t, int lane,
+                                             SersicTables<kChi2Chunk<GRAD>>& tab,
+                                             const Trial<double>& t, int lane,
                                              Acc<GRAD ? 0xFFu : 0u, double>& acc) {
   auto uni = [](double v) { return Arith<double>::uni(v); };
   // The constants are read from LDS where they are used, so that the pixel loop
   // holds only its own (all in registers they spilled).
   const double beta = uni(t.ha - 1.0), I0 = uni(t.I0), k5a = uni(t.k5a), qa = uni(t.qa);
   const double sky = in_vgpr(t.sky), k5b = in_vgpr(t.k5b);
-  if constexpr (COVERED) {
-    wave_sync();   // the previous stamp's reads of the tables are done
-    const int e = kPowExpLo + lane;
-    tab.E[(e + 1023) & (kPowExp - 1)] = exp2_series(fma(beta, (double)e, t.hc));
+  wave_sync();   // the previous stamp's reads of the tables are done
+  const int e0 = kPowExpLo + lane;
+  tab.E[(e0 + 1023) & (kPowExp - 1)] = exp2_series(fma(beta, (double)e0, t.hc));
 #pragma unroll 1
-    for (int j = lane; j < kPowTab; j += kWave)
-      tab.at[j].pow = exp2_series(beta * (tab.at[j].log + 1.0));
-    wave_sync();
-  }
+  for (int j = lane; j < kPowTab; j += kWave)
+    tab.at[j].pow = exp2_series(beta * (tab.at[j].log + 1.0));
+  wave_sync();
   // binomial coefficients of (1 + r)^beta
   const double b2 = uni(beta * (beta - 1.0) * 0.5), b3 = uni(b2 * (beta - 2.0) * (1.0 / 3.0));
   const double b4 = in_vgpr(b3 * (beta - 3.0) * 0.25), b5 = uni(b4 * (beta - 4.0) * 0.2);
@@ -187,31 +181,27 @@ __device__ __forceinline__ void sersic_sweep(const shape_batch& b, const Stamp& 
     auto pixel = [&](float raw) {
       const double R2 = fma(fma(qa, u2, qb), u2, qc);
       SersicPowers w;
-      if constexpr (COVERED) {
-        const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, R2) >> 32);
-        // the interval (7 bits of the fraction) and the exponent's low 6 bits
-        const auto& iv = at_byte(tab.at, (hi >> 8) & ((kPowTab - 1) * 32u));
-        const double Ee = at_byte(tab.E, (hi >> 17) & ((kPowExp - 1) * 8u));
-        const double r = fma(__builtin_amdgcn_frexp_mant(R2), iv.rcp, -1.0);
-        const double pw = fma(fma(fma(fma(fma(b5, r, b4), r, b3), r, b2), r, beta), r, 1.0);
-        w.tr = Ee * iv.pow * pw;
-        w.t = w.tr * R2;
-        // m0 = e^z, z = -b t = K ln 2 / 64 + y (cut at z = -740, where m0 c is 0);
-        // 24 e^y = 24 + 24 y + 12 y^2 + 4 y^3 + y^4: two of the constants are
-        // free as operands
-        const double tc = fmin(w.t, tmax), K = __builtin_rint(zk * tc);
-        const int ki = (int)K;
-        const double y = fma(K, -kLn2 / kF64Tab, zb * tc);
-        const double ey = fma(fma(fma(y + 4.0, y, 12.0), y, 24.0), y, 24.0);
-        w.m0 = __builtin_ldexp(at_byte(tab.ex, ((uint32_t)ki << 3) & ((kF64Tab - 1) * 8u)) * ey,
-                               ki >> 6);
-        if constexpr (GRAD) {
-          // log2 R^2 = e + log2 c_j + log2 e ln(1 + r), 4 ln(1 + r) / r in q
-          const double q = fma(fma(fma(fma(0.8, r, -1.0), r, 4.0 / 3.0), r, -2.0), r, 4.0);
-          w.L = fma(r * q, 0.25 * kLog2e, (double)__builtin_amdgcn_frexp_exp(R2) + iv.log);
-        }
-      } else {
-        w = sersic_powers(t, R2);
+      const uint32_t hi = (uint32_t)(__builtin_bit_cast(uint64_t, R2) >> 32);
+      // the interval (7 bits of the fraction) and the exponent's low 6 bits
+      const auto& iv = at_byte(tab.at, (hi >> 8) & ((kPowTab - 1) * 32u));
+      const double Ee = at_byte(tab.E, (hi >> 17) & ((kPowExp - 1) * 8u));
+      const double r = fma(__builtin_amdgcn_frexp_mant(R2), iv.rcp, -1.0);
+      const double pw = fma(fma(fma(fma(fma(b5, r, b4), r, b3), r, b2), r, beta), r, 1.0);
+      w.tr = Ee * iv.pow * pw;
+      w.t = w.tr * R2;
+      // m0 = e^z, z = -b t = K ln 2 / 64 + y (cut at z = -740, where m0 c is 0);
+      // 24 e^y = 24 + 24 y + 12 y^2 + 4 y^3 + y^4: two of the constants are
+      // free as operands
+      const double tc = fmin(w.t, tmax), K = __builtin_rint(zk * tc);
+      const int ki = (int)K;
+      const double y = fma(K, -kLn2 / kF64Tab, zb * tc);
+      const double ey = fma(fma(fma(y + 4.0, y, 12.0), y, 24.0), y, 24.0);
+      w.m0 = __builtin_ldexp(at_byte(tab.ex, ((uint32_t)ki << 3) & ((kF64Tab - 1) * 8u)) * ey,
+                             ki >> 6);
+      if constexpr (GRAD) {
+        // log2 R^2 = e + log2 c_j + log2 e ln(1 + r), 4 ln(1 + r) / r in q
+        const double q = fma(fma(fma(fma(0.8, r, -1.0), r, 4.0 / 3.0), r, -2.0), r, 4.0);
+        w.L = fma(r * q, 0.25 * kLog2e, (double)__builtin_amdgcn_frexp_exp(R2) + iv.log);
       }
       const double m0 = w.m0;
       const double d = residual<DT>(raw, st.scale, fma(I0, m0, sky));

@@ -102,3 +102,75 @@ def test_chunks_of_stamps_do_not_change_the_results(shape):
         small, large = (o[key].cpu().numpy() for o in out)
         np.testing.assert_array_equal(large.reshape((1025,) + small.shape),
                                       np.broadcast_to(small, (1025,) + small.shape))
+
+
+# Stamps at the ends of what the tables cover: ellipticity, index and size, the
+# cut at b t = 740 (small sizes and indices), a centre far off and one just above
+# the smallest R^2.  (x0, y0 from the middle pixel; e1, e2; Re; n.)
+TABLE_ENDS = [(0.3, 0.4, 0.95, 0.0, 9.0, 2.0), (0.3, 0.4, 0.0, -0.95, 9.0, 0.6),
+              (0.45, 0.35, 0.998, 0.0, 9.0, 1.0), (0.45, 0.35, -0.7, 0.711, 9.0, 4.0),
+              (0.3, 0.4, 0.2, 0.1, 9.0, 0.15), (0.3, 0.4, 0.2, 0.1, 9.0, 18.0),
+              (0.3, 0.4, 0.2, 0.1, 0.002, 4.0), (0.3, 0.4, 0.2, 0.1, 0.05, 0.5),
+              (0.3, 0.4, 0.2, 0.1, 0.3, 0.2), (0.3, 0.4, 0.2, 0.1, 9e4, 1.0),
+              (0.3, 0.4, 0.2, 0.1, 9e4, 0.3), (-4000.3, 700.4, 0.2, 0.1, 900.0, 1.5),
+              (4e-4, 0.0, 0.0, 0.0, 9.0, 1.0), (4e-4, 0.0, 0.0, 0.0, 9.0, 6.0)]
+
+
+@pytest.mark.parametrize("storage", ["f32", "f16"])
+@pytest.mark.parametrize("side", [48, 64, 100])
+def test_sersic_tables_at_the_ends_of_their_range(shape, side, storage):
+    """1e-6 as above (at |e| = 0.998 the quadratics of R^2 would cancel to 1e-16 (2 /
+    0.002)^2 = 1e-10), beside FP32's smallest normal number, 1.2e-38."""
+    import torch
+    n = len(TABLE_ENDS)
+    rng = np.random.default_rng(side)
+    p = np.empty((n, 8))
+    p[:, :6] = TABLE_ENDS
+    p[:, 0:2] += side // 2
+    p[:, 6] = rng.uniform(1.0, 100.0, n)
+    p[:, 7] = rng.uniform(-5.0, 5.0, n)
+    p = p.astype(np.float32).astype(np.float64)
+    pix = rng.normal(3.0, 2.0, (n, side, side)).astype(np.float16 if storage == "f16" else np.float32)
+    sigma = rng.uniform(1.0, 3.0, n).astype(np.float32)
+    db = shape.DeviceBatch(pixels=torch.from_numpy(pix).cuda().reshape(-1),
+                           sigma=torch.from_numpy(sigma).cuda(), side0=side,
+                           scale=torch.full((n,), 0.5, device="cuda") if storage == "f16" else None)
+    pt = torch.from_numpy(p.astype(np.float32)).cuda()
+    value = shape.chi2_fwd(db, pt).cpu().numpy()
+    got = {k: v.cpu().numpy() for k, v in shape.chi2_bwd(db, pt, want_normal=True).items()}
+    img = pix.astype(np.float64) * (0.5 if storage == "f16" else 1.0)
+    for s in range(n):
+        c2, g, jtj = oracle.chi2(img[s], float(sigma[s]), p[s], want_grad=True)
+        assert abs(value[s] / c2 - 1) < 1e-6, s
+        err = _check_grad(got["grad"][s:s + 1].astype(np.float64), g[None], p[s:s + 1], sigma[s:s + 1])
+        assert err < 1e-6, (s, err)
+        d = np.sqrt([jtj[k * 8 - k * (k - 1) // 2] for k in range(8)])
+        unit = np.array([d[k] * d[m] for k in range(8) for m in range(k, 8)])
+        tol = 1e-6 * np.maximum(np.abs(jtj), 1e-3 * unit) + 1.2e-38
+        assert (np.abs(got["jtj"][s] - jtj) <= tol).all(), s
+
+
+def test_bad_stamps_beside_good_ones(shape):
+    """Several stamps to a workgroup (over 16,384 of them): those that cannot be
+    evaluated give NaN, and their neighbours what they give in a small batch."""
+    import torch
+    p, pix, sigma = _stamps(48, "f32")
+    k = 1025
+    t = lambda x: torch.from_numpy(np.tile(x, (k,) + (1,) * (x.ndim - 1))).cuda()   # noqa: E731
+    bad = np.zeros(16 * k, bool)
+    bad[[0, 7, 8, 4097, 4098, 16 * k - 1]] = True
+    good_sigma, model = t(sigma), np.zeros(16 * k, np.uint8)
+    bad_sigma = torch.where(torch.from_numpy(bad).cuda(), -good_sigma, good_sigma)
+    model[5000] = 7                                     # no such model
+    bad[5000] = True
+    small = shape.DeviceBatch(pixels=torch.from_numpy(pix).cuda().reshape(-1),
+                              sigma=torch.from_numpy(sigma).cuda(), side0=48)
+    large = shape.DeviceBatch(pixels=t(pix).reshape(-1), sigma=bad_sigma, side0=48,
+                              model=torch.from_numpy(model).cuda())
+    par = torch.from_numpy(p.astype(np.float32)).cuda()
+    a = shape.chi2_bwd(small, par, want_normal=True)
+    b = shape.chi2_bwd(large, par.repeat(k, 1), want_normal=True)
+    for key in ("chi2", "grad", "jtj", "jtr"):
+        x, y = a[key].cpu().numpy(), b[key].cpu().numpy()
+        assert np.isnan(y[bad]).all()
+        np.testing.assert_array_equal(y[~bad], x[np.arange(16 * k) % 16][~bad])
