@@ -234,3 +234,36 @@ def test_small_frames_are_read_by_one_workgroup_each(shape, H, W, f16):
     for k in ref:
         np.testing.assert_array_equal(g[k], ref[k], err_msg=k)
         np.testing.assert_array_equal(out[k].cpu().numpy(), ref[k], err_msg=k)
+
+
+# Equal maxima by the pixel (in FP32 batches of 4,096 and chunks of 8,192 pixels; in
+# FP16 8,192 and 32,768): in one vector, in two batches of one thread, in a chunk's
+# ragged last batch, in the next chunk, in records 256 apart (which one thread of the
+# combining workgroup holds), and in the last pixels.
+@pytest.mark.parametrize("H,W,f16", [(1531, 1401, False), (2999, 2903, True), (517, 333, False),
+                                     (517, 333, True)])
+def test_first_of_equal_maxima_in_split_frames(shape, H, W, f16):
+    rng = np.random.default_rng(H)
+    npix, batch, chunk = H * W, 8192 if f16 else 4096, 32768 if f16 else 8192
+    parts = -(-npix // chunk)
+    chunk = -(-(-(-npix // parts)) // batch) * batch
+    assert (-(-npix // chunk) > 256) == (H > 1000)
+    last = (npix - 1) // chunk * chunk
+    sets = [[1000, 1001], [5 + 4 * 7, 5 + 4 * 7 + batch], [batch - 1, batch], [chunk - 1, chunk],
+            [chunk + 9, 2 * chunk + 1, 9 + batch], [last - 1, last, npix - 1], [npix - 2, npix - 1],
+            [W, npix // 2]]
+    if H > 1000:
+        sets += [[3 + chunk, 3 + 257 * chunk], [257 * chunk, 2 * chunk], [0, chunk, 256 * chunk]]
+    pix = rng.normal(10.0, 1.0, (len(sets), npix)).astype(np.float16 if f16 else np.float32)
+    for k, at in enumerate(sets):
+        pix[k, at] = 900.0
+    fr, g = _gpu_detect(shape, pix.reshape(-1, H, W), scale=np.ones(len(sets), np.float32) if f16 else None)
+    ref = _one_group_per_frame(shape, fr)
+    first = np.array([min(at) for at in sets])
+    np.testing.assert_array_equal(g["peak"], np.stack([first % W, first // W], 1))
+    for k in ("peak", "box", "status"):
+        np.testing.assert_array_equal(g[k], ref[k], err_msg=k)
+    # sky: an FP64 mean in another order; F: sums of H W terms of at most 900
+    np.testing.assert_allclose(g["info"][:, 0], ref["info"][:, 0], rtol=2.0 ** -22)
+    assert (np.abs(g["info"][:, 2] - ref["info"][:, 2])
+            <= 2.0 ** -22 * np.abs(ref["info"][:, 2]) + 2.0 ** -50 * npix * 900.0).all()
