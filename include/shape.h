@@ -406,10 +406,13 @@ int shape_frame_detect(const shape_frames* frames, int32_t max_side, float* info
  * The same with scratch memory of the caller's: the frames are read by as many
  * workgroups as the card takes, not by one each, so a few large frames take
  * microseconds where shape_frame_detect takes most of a millisecond.  The
- * same outputs (sky and F are the same FP64 sums in another order, so their
- * FP32 values may differ in the last bit).  ws (device, 16-byte aligned) is
- * free again once the stream has passed the call; its contents are not used
- * between calls.
+ * same outputs, but for rounding: sky is the same FP64 sum in another order,
+ * and F is formed as sum I - H W sky, each good to about H W max|I| 2^-50
+ * absolutely, which is more than F's last FP32 bit where F is a small remainder
+ * of large pixels; r50, the box and NONPOSITIVE_FLUX follow from F.  A frame's
+ * outputs do not depend on the other frames of the call.  ws (device, 16-byte
+ * aligned) is free again once the stream has passed the call; its contents are
+ * not used between calls.
  *   shape_frame_workspace_bytes: the bytes ws needs for these frames (a
  *   function of n, height, width and dtype).
  * Frames of at most SHAPE_FRAME_WHOLE pixels are read by one workgroup each all
