@@ -22,12 +22,13 @@
 //
 // Measured against the lane-stride or row-layout sweep by 64-point log2 and
 // exp2 tables, one wave per stamp (us; chi^2 / with gradient / with the normal
-// matrix): 65,536 of 64 x 64 FP32 628 / 809 / 1,170 -> 463 / 656 / 961, FP16
-// 623 / 796 / 1,112 -> 433 / 614 / 937; 20,000 of 48 x 48 FP16 129 / 184 / 256 ->
-// 97 / 130 / 213; 8,000 of 128 x 128 357 / 495 / 720 -> 243 / 326 / 468.  Smaller
-// stamps and mixed sides keep that sweep (adjoint.hip).  40, 62 and 88 VALU
-// instructions per pixel and 500 to 1,000 per stamp; the SIMDs issue on about
-// 90% of cycles.
+// matrix): 65,536 of 64 x 64 FP32 585 / 812 / 1,178 -> 469 / 666 / 978, FP16
+// 573 / 788 / 1,099 -> 434 / 621 / 947; 20,000 of 48 x 48 FP16 129 / 185 / 255 ->
+// 97 / 130 / 213; 8,000 of 128 x 128 FP32 354 / 491 / 723 -> 228 / 313 / 446.
+// Smaller stamps and mixed sides keep that sweep (adjoint.hip).  On the 64 x 64
+// FP32 batch the counters give 47, 70 and 107 VALU instructions per pixel, the
+// work per stamp and per item among them, issued in 0.75, 0.76 and 0.79 of the
+// SIMDs' slots of four cycles (a loop of FP64 FMAs on registers reaches 0.84).
 #pragma once
 
 #include "sweep.hpp"
