@@ -66,8 +66,10 @@ __global__ __launch_bounds__(kWave, SHAPE_FIT_WAVES_PER_SIMD) void fit_kernel(
         lm_fit<DT, MODEL, MASK, 1, kLayoutAny | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2,
                                                      perr, iters, status, sweeps, tid);
     } else {
-      lm_fit<DT, MODEL, MASK, 1, LAYOUT | kLayoutFloorFree, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr,
-                                               iters, status, sweeps, tid);
+      constexpr int kForm =
+          LAYOUT | kLayoutFloorFree | (LAYOUT == kLayoutRows ? kLayoutAhead : 0);
+      lm_fit<DT, MODEL, MASK, 1, kForm, PROF>(b, o, st, p_init, rec, s, W, p_out, chi2, perr, iters,
+                                              status, sweeps, tid);
     }
     __syncthreads();  // W (and the staged stamp) are reused by the next stamp of this wave
   }

@@ -564,6 +564,8 @@ constexpr int kLayoutSegsOnly = 5;
 // kLayoutFloorFree: with kLayoutRows, kLayoutAny or kLayoutSegsOnly, two copies of
 // the loops, of which one has no test for the model's floor (clear_of_floor).
 constexpr int kLayoutFloorFree = 16;
+// kLayoutAhead: with kLayoutRows, rows loaded ahead of their use.
+constexpr int kLayoutAhead = 32;
 
 __host__ __device__ inline constexpr bool rows_layout_fits(int side) {
   return side == 8 || side == 16 || side == 32 || side == 64;
@@ -611,7 +613,7 @@ template <int DT, int MODEL, uint32_t EM, int STRIDE = kWave, typename T = float
 __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, const Trial<T>& t,
                              Acc<EM, T>& acc, int tid = -1, void* stage = nullptr) {
   using A = Arith<T>;
-  constexpr int LAYOUT = FORM & ~kLayoutFloorFree;
+  constexpr int LAYOUT = FORM & ~(kLayoutFloorFree | kLayoutAhead);
   constexpr int kFlush = sizeof(T) == 4 ? SHAPE_SWEEP_FLUSH : 0;
   constexpr bool kGrad = (SUMS & kSumsGradient) != 0u;   // chi^2 and J^T r
   acc.c2 = 0.0;
@@ -815,15 +817,23 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
     const int nstep = st.npix / kWave;
     const void* sp = stamp_base<DT>(b, st);
     // FP32 stamps in memory, whole runs of kRun rows (sides 32 and 64): the
-    // run is unrolled, so its loads issue together, and in the FP32 instance
-    // its first pixel opens the partials (2 fewer VALU per pixel); measured
-    // on 262,144 64 x 64 stamps: fit 23.1 -> 20.8 ms, 32 x 32 4-parameter fit
-    // 3.72 -> 2.83 ms; FP64 chi^2 0.74 -> 0.72 ms, with J^T J 1.47 -> 1.33 ms
-    // (65,536 stamps).  FP16 stamps staged in LDS ran 5% slower unrolled (4%
-    // in the moment form: 18.1 vs 17.5 ms) and keep the loop, as does the
-    // FP64 gradient without J^T J, whose five waves per SIMD leave the
-    // unrolled run too few registers (136 spilled, 4x slower).
+    // run is unrolled, and in the FP32 instance its first pixel opens the
+    // partials (2 fewer VALU per pixel); measured on 262,144 64 x 64 stamps: fit
+    // 23.1 -> 20.8 ms, 32 x 32 4-parameter fit 3.72 -> 2.83 ms; FP64 chi^2 0.74 ->
+    // 0.72 ms, with J^T J 1.47 -> 1.33 ms (65,536 stamps).  FP16 stamps staged in
+    // LDS ran 5% slower unrolled (4% in the moment form: 18.1 vs 17.5 ms) and keep
+    // the loop, as does the FP64 gradient without J^T J, whose five waves per SIMD
+    // leave the unrolled run too few registers (136 spilled, 4x slower).
+    // The fused fit (kLayoutAhead) loads a run's rows four ahead of their use, held
+    // there by scheduling barriers that only arithmetic crosses: left to itself
+    // the compiler puts each load a few instructions before its use, and stamps
+    // that the L2 does not hold wait for every one: 262,144 of 64 x 64 18.9 -> 17.6
+    // ms, their 4-parameter fit 14.8 -> 9.8 (32 x 32, which it holds, 7.92 -> 7.96 and
+    // 4.35 -> 4.34).  All eight at the run's start 17.9 and 9.9, the next run's held
+    // over this one 20.2 and 11.2.  The queue keeps the compiler's order: its drain
+    // of 200,000 of 32 x 32, 4 parameters, 10.2 -> 11.4 ms.
     constexpr int kRun = 8;
+    constexpr int kAhead = (FORM & kLayoutAhead) ? 4 : 0;
     static_assert(kFlush == 0 || kFlush == kRun, "a run is one partial-sum block");
     // The sweeps of part of the sums (SUMS), one wave per SIMD with registers to
     // spare, are unrolled in either storage.
@@ -846,9 +856,18 @@ __device__ __forceinline__ void sweep(const shape_batch& b, const Stamp& st, con
       if (blocked) {
 #pragma unroll 1
         for (int m0 = 0; m0 < nstep; m0 += kRun) {
+          float raw[kRun];
+          auto load = [&](int q) { raw[q] = load_raw<DT>(sp, k + (uint32_t)(q * kWave)); };
+          if constexpr (kAhead > 0) {
+#pragma unroll
+            for (int q = 0; q < kAhead; ++q) load(q);
+          }
 #pragma unroll
           for (int q = 0; q < kRun; ++q) {
-            row_pixel(RunFused(), flr, load_raw<DT>(sp, k + (uint32_t)(q * kWave)), u2, q == 0);
+            if constexpr (kAhead > 0) __builtin_amdgcn_sched_barrier(1);
+            if (q + kAhead < kRun) load(q + kAhead);
+            if constexpr (kAhead > 0) __builtin_amdgcn_sched_barrier(1);
+            row_pixel(RunFused(), flr, raw[q], u2, q == 0);
             u2 += di;
           }
           k += (uint32_t)(kRun * kWave);

@@ -56,6 +56,21 @@ def test_queue_equals_fused_fit(shape, workload):
             assert q["drained"] and q["steps"] == 2
 
 
+@pytest.mark.parametrize("mask", [0xFF, 0xF0])
+@pytest.mark.parametrize("workload", ["plain32x", "sersic64"])
+def test_fused_fit_of_row_runs_equals_queue(shape, workload, mask):
+    """FP32 stamps of 32 x 32 and 64 x 64 (two and eight runs of rows to a
+    column): the fused fit, which loads a run's rows ahead, equals the queue's
+    steps, which do not, bit for bit."""
+    db = shape.DeviceBatch.from_host(synth.make(workload, count=700), "cuda:0")
+    o = shape.default_opts(free_mask=mask)
+    rec = _moments(shape, db, o)
+    fused = _np(shape.fit_sersic(db, rec=rec, opts=o))
+    q = _np(shape.fit_queue(db, rec=rec, opts=o, cfg=shape.queue_cfg(team=1), drain_at=0))
+    for k in ("p", "chi2", "iters", "status", "sweeps"):
+        np.testing.assert_array_equal(q[k], fused[k], err_msg=k)
+
+
 @pytest.mark.parametrize("grid,chunk", [(1, 0), (3, 1), (8, 0), (100, 64)])
 def test_queue_small_grids(shape, grid, chunk):
     """Persistent grids smaller than the cursor count still drain every cursor
